@@ -9,12 +9,32 @@
 #include "lbm_kernel_util.hpp"
 
 namespace lbm {
-// Missing link d at a wall node of edge e (eq:boundary-general):
-// f_d = D f*_{-d}(X) + S_d, velocity rule eq:dirichlet-boundary-rule,
-// traction rule eq:neumann-boundary-rule.  In shifted storage only the traction F rows
-// change: g_d = -g*_{-d} + (F^b - I)/2 (F^b arrives from the staging buffer as F^b - I).
-// ownp points at the node's first population, plane stride `stride` (the tiled array or a
-// wall line of the staging buffer).
+// Missing link d at a wall node (eq:boundary-general): f_d = D f*_{-d}(X) + S_d, velocity
+// rule eq:dirichlet-boundary-rule, traction rule eq:neumann-boundary-rule.  o: the node's
+// outgoing populations f*_{-d}; (N0, N1): the edge's outward normal; w: the boundary data;
+// Fb: F^b of the link (traction rule; F^b - I in shifted storage, where only the traction F
+// rows change: g_d = -g*_{-d} + (F^b - I)/2).
+template <typename R>
+__device__ __forceinline__ void wall_rule(bool velocity, R N0, R N1, R w0, R w1, R c, const R o[6], const R Fb[4],
+                                          R out[6]) {
+    if (velocity) {
+        out[0] = -o[0] + R(0.5) * w0;
+        out[1] = -o[1] + R(0.5) * w1;
+        out[2] = o[2] + N0 * w0 / c;
+        out[3] = o[3] + N1 * w0 / c;
+        out[4] = o[4] + N0 * w1 / c;
+        out[5] = o[5] + N1 * w1 / c;
+    } else {
+        out[0] = o[0] + w0 / c;
+        out[1] = o[1] + w1 / c;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) out[2 + k] = -o[2 + k] + R(0.5) * Fb[k];
+    }
+}
+
+// The missing link of edge e at position s, F^b from the staging buffer.  ownp points at the
+// node's first population, plane stride `stride` (the tiled array or a wall line of the
+// staging buffer).
 template <typename T, typename R>
 __device__ __forceinline__ void wall_link(const Common& cm, const EdgeData& ed, const void* auxp,
                                           int e, int s, const T* ownp, int64_t stride, R out[6]) {
@@ -24,24 +44,17 @@ __device__ __forceinline__ void wall_link(const Common& cm, const EdgeData& ed, 
 #pragma unroll
     for (int k = 0; k < 6; ++k) o[k] = R(ownp[(6 * G.od + k) * stride]);
     const R w0 = edge_value<R>(ed, e, 0, s, L), w1 = edge_value<R>(ed, e, 1, s, L);
-    const R c = R(cm.c);
-    if (cm.bc[e] == LBM_VELOCITY) {
-        const R N0 = (G.A == 0) ? R(G.NA) : R(0), N1 = (G.A == 1) ? R(G.NA) : R(0);
-        out[0] = -o[0] + R(0.5) * w0;
-        out[1] = -o[1] + R(0.5) * w1;
-        out[2] = o[2] + N0 * w0 / c;
-        out[3] = o[3] + N1 * w0 / c;
-        out[4] = o[4] + N0 * w1 / c;
-        out[5] = o[5] + N1 * w1 / c;
-    } else {
+    const R N0 = (G.A == 0) ? R(G.NA) : R(0), N1 = (G.A == 1) ? R(G.NA) : R(0);
+    R Fb[4] = {R(0), R(0), R(0), R(0)};
+    const bool velocity = cm.bc[e] == LBM_VELOCITY;
+    if (!velocity) {
         int off[4], len[4];
         edge_offsets(cm.nx, cm.ny, off, len);
-        const R* Fb = (const R*)auxp + 4 * (int64_t)(off[e] + s);
-        out[0] = o[0] + w0 / c;
-        out[1] = o[1] + w1 / c;
+        const R* p = (const R*)auxp + 4 * (int64_t)(off[e] + s);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) out[2 + k] = -o[2 + k] + R(0.5) * Fb[k];
+        for (int k = 0; k < 4; ++k) Fb[k] = p[k];
     }
+    wall_rule<R>(velocity, N0, N1, w0, w1, R(cm.c), o, Fb, out);
 }
 
 // One node's update from its pulled populations g: moments with the half-step source

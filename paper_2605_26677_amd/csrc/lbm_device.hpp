@@ -322,6 +322,14 @@ __device__ __forceinline__ void to_shift(const R f[4], R fs[4]) {
 // reported as 0 for a Gent state beyond the limit A < J_m, so that every caller's J > 0
 // test also rejects it).
 
+// P of log-NH and NH from the kinematics of the state.
+template <typename R, int LAW>
+__device__ __forceinline__ void piola_lame(const Kin<R>& k, R mu, R lam, R P[4], R& J) {
+    const R vol = (LAW == LBM_LOGNH) ? lam * k.L : R(0.5) * lam * k.Jsq_m1;
+    for (int a = 0; a < 4; ++a) P[a] = mu * k.FmH[a] + vol * k.H[a];
+    J = k.J;
+}
+
 template <typename R, int LAW, bool SHIFTED>
 __device__ __forceinline__ void piola(const R f[4], R mu, R lam, const LawK<R>& lk, R P[4], R& J) {
     if constexpr (invariant_law<LAW>()) {
@@ -344,10 +352,7 @@ __device__ __forceinline__ void piola(const R f[4], R mu, R lam, const LawK<R>& 
         if constexpr (SHIFTED) J = R(1) + (f[0] + f[3] + (f[0] * f[3] - f[1] * f[2]));
         else J = f[0] * f[3] - f[1] * f[2];
     } else {
-        const Kin<R> k = kinematics<R, SHIFTED>(f);
-        const R vol = (LAW == LBM_LOGNH) ? lam * k.L : R(0.5) * lam * k.Jsq_m1;
-        for (int a = 0; a < 4; ++a) P[a] = mu * k.FmH[a] + vol * k.H[a];
-        J = k.J;
+        piola_lame<R, LAW>(kinematics<R, SHIFTED>(f), mu, lam, P, J);
     }
 }
 

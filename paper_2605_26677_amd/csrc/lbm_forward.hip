@@ -18,10 +18,8 @@
 
 namespace lbm {
 
-// F^b of every link of the traction edges at step n -> n+1 (Sec. 3.6).  Reading of the
-// interior values the paper takes F^b's tangential column from: the wall node's own F of
-// level n (recovered from its stored populations); the Newton solve of the traction
-// equations starts from that node's normal column.
+// F^b of every link of the traction edges at step n -> n+1 (Sec. 3.6; boundary_F), from the
+// wall nodes' stored populations of level n.
 //
 // One launch covers every traction edge (each edge reads level n only and writes its own
 // slice of the staging buffer), one wavefront per workgroup and one lane per link: the
@@ -38,7 +36,6 @@ __device__ __forceinline__ void traction_solve(const TractionArgs& a, int e) {
     const Common& cm = a.cm;
     const EdgeGeom G = edge_geom(e);
     const int L = (AX == 0) ? cm.ny : cm.nx;
-    constexpr int Bx = 1 - AX;
     const int s = (int(blockIdx.x) - a.eblk[e]) * kTracWin + int(threadIdx.x);
     if (s >= L) return;
     const int64_t n = int64_t(cm.nx) * cm.ny;
@@ -56,22 +53,13 @@ __device__ __forceinline__ void traction_solve(const TractionArgs& a, int e) {
     } else {
         recover_node<T, R>((const T*)a.pop, cm.ntile, n0.x, n0.y, hdt * R(b0), hdt * R(b1), Uw);
     }
-    R tang[2], acol[2], Tv[2];
-    for (int k = 0; k < 2; ++k) {
-        tang[k] = Uw[2 + 2 * k + Bx];
-        acol[k] = Uw[2 + 2 * k + AX];
-        Tv[k] = edge_value<R>(a.ed, e, k, s, L);
-    }
-    R mu, lam;
+    const R Tv[2] = {edge_value<R>(a.ed, e, 0, s, L), edge_value<R>(a.ed, e, 1, s, L)};
+    R mu, lam, Fb[4];
     params_at<FIELDS, R>(cm, n0.y * cm.nx + n0.x, mu, lam);
-    const bool ok = newton_column<R, LAW, SH, AX>(R(G.NA), tang, Tv, mu, lam, law_consts<R>(cm), acol,
-                                                 cm.newton_max_iter, R(cm.newton_tol));
-    if (!ok) atomicOr(cm.fault, (uint32_t)LBM_FAULT_NEWTON);
+    if (!boundary_F<R, LAW, SH, AX>(cm, R(G.NA), Uw, Tv, mu, lam, Fb)) atomicOr(cm.fault, (uint32_t)LBM_FAULT_NEWTON);
     R* aux = (R*)a.aux + 4 * (int64_t)(edge_off(cm.nx, cm.ny, e) + s);
-    for (int k = 0; k < 2; ++k) {
-        aux[2 * k + AX] = acol[k];
-        aux[2 * k + Bx] = tang[k];
-    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) aux[k] = Fb[k];
 }
 
 template <int ST, int LAW, bool FIELDS, bool LINES>

@@ -116,10 +116,17 @@ __device__ bool newton_column(R NA, const R tang[2], const R T[2], R mu, R lam,
         f[A] = ac[0]; f[2 + A] = ac[1];
         f[B] = tang[0]; f[2 + B] = tang[1];
     };
-    auto resid = [&](const R ac[2], R r[2], R& J) {
+    // log-NH and NH: the kinematics of an accepted point serve its residual and its tangent
+    constexpr bool kLame = LAW == LBM_LOGNH || LAW == LBM_NH;
+    auto resid = [&](const R ac[2], R r[2], R& J, Kin<R>& kin) {
         R f[4], P[4];
         assemble(ac, f);
-        piola<R, LAW, SH>(f, mu, lam, lk, P, J);
+        if constexpr (kLame) {
+            kin = kinematics<R, SH>(f);
+            piola_lame<R, LAW>(kin, mu, lam, P, J);
+        } else {
+            piola<R, LAW, SH>(f, mu, lam, lk, P, J);
+        }
         r[0] = NA * P[A] - T[0];
         r[1] = NA * P[2 + A] - T[1];
     };
@@ -131,14 +138,20 @@ __device__ bool newton_column(R NA, const R tang[2], const R T[2], R mu, R lam,
         else s2 = (f[0] - R(1)) * (f[0] - R(1)) + f[1] * f[1] + f[2] * f[2] + (f[3] - R(1)) * (f[3] - R(1));
         return sqrt_r(T[0] * T[0] + T[1] * T[1]) + mu * sqrt_r(s2);
     };
+    // With the plain F the residual cannot drop below the rounding of terms of size
+    // |T| + 2 mu (P subtracts O(mu) quantities); the shifted form has no such floor.
+    const R eps = sizeof(R) == 8 ? R(2.220446049250313e-16) : R(1.1920929e-7);
+    const R round = SH ? R(0) : eps * (sqrt_r(T[0] * T[0] + T[1] * T[1]) + R(2) * mu);
     R r[2], J;
-    resid(a, r, J);
+    Kin<R> kin;
+    resid(a, r, J, kin);
     for (int it = 0; it < max_iter; ++it) {
         const R rn = sqrt_r(r[0] * r[0] + r[1] * r[1]);
         if (rn <= tol * scale(a)) break;
         R f[4], C[16];
         assemble(a, f);
-        tangent<R, LAW, SH>(f, mu, lam, lk, C);
+        if constexpr (kLame) tangent_lame<R, LAW>(kin, mu, lam, C);
+        else tangent<R, LAW, SH>(f, mu, lam, lk, C);
         const R j00 = NA * C[4 * A + A], j01 = NA * C[4 * A + 2 + A];
         const R j10 = NA * C[8 + 4 * A + A], j11 = NA * C[8 + 4 * A + 2 + A];
         const R det = j00 * j11 - j01 * j10;
@@ -146,14 +159,20 @@ __device__ bool newton_column(R NA, const R tang[2], const R T[2], R mu, R lam,
         const R d1 = -(-j10 * r[0] + j00 * r[1]) / det;
         R alpha = R(1);
         bool accepted = false;
-        for (int ls = 0; ls < 11; ++ls) {
+        // at that floor |r| is rounding noise, and a shorter step only draws it again: the full
+        // step alone decides (the eleven vain trials of the last iteration made three
+        // quarters of an FP64 solve)
+        const int trials = rn <= R(16) * round ? 1 : 11;
+        for (int ls = 0; ls < trials; ++ls) {
             const R trial[2] = {a[0] + alpha * d0, a[1] + alpha * d1};
             R rt[2], Jt;
-            resid(trial, rt, Jt);
+            Kin<R> kt;
+            resid(trial, rt, Jt, kt);
             if (Jt > R(0) && sqrt_r(rt[0] * rt[0] + rt[1] * rt[1]) < rn) {
                 a[0] = trial[0]; a[1] = trial[1];
                 r[0] = rt[0]; r[1] = rt[1];
                 J = Jt;
+                kin = kt;
                 accepted = true;
                 break;
             }
@@ -162,11 +181,31 @@ __device__ bool newton_column(R NA, const R tang[2], const R T[2], R mu, R lam,
         if (!accepted) break;
     }
     const R rn = sqrt_r(r[0] * r[0] + r[1] * r[1]);
-    // With the plain F the residual cannot drop below the rounding of terms of size
-    // |T| + 2 mu (P subtracts O(mu) quantities); the shifted form has no such floor.
-    const R eps = sizeof(R) == 8 ? R(2.220446049250313e-16) : R(1.1920929e-7);
-    const R floor = SH ? R(0) : R(1e3) * eps * (sqrt_r(T[0] * T[0] + T[1] * T[1]) + R(2) * mu);
-    return (rn <= R(1e-4) * scale(a) + floor) && (J > R(0)) && finite_r(rn);
+    return (rn <= R(1e-4) * scale(a) + R(1e3) * round) && (J > R(0)) && finite_r(rn);
+}
+
+// F^b of a traction link (Sec. 3.6) from the state U of its wall node at level n, boundary
+// traction Tv and the node's parameters.  Reading of the interior values the paper takes
+// F^b's tangential column from: the wall node's own F of level n; the Newton solve of the
+// traction equations starts from that node's normal column.  Returns false on failure.
+template <typename R, int LAW, bool SH, int AX>
+__device__ __forceinline__ bool boundary_F(const Common& cm, R NA, const R U[6], const R Tv[2], R mu, R lam,
+                                           R Fb[4]) {
+    constexpr int Bx = 1 - AX;
+    R tang[2], acol[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        tang[k] = U[2 + 2 * k + Bx];
+        acol[k] = U[2 + 2 * k + AX];
+    }
+    const bool ok = newton_column<R, LAW, SH, AX>(NA, tang, Tv, mu, lam, law_consts<R>(cm), acol,
+                                                 cm.newton_max_iter, R(cm.newton_tol));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        Fb[2 * k + AX] = acol[k];
+        Fb[2 * k + Bx] = tang[k];
+    }
+    return ok;
 }
 
 // Node (x, y) of row r (0 = wall row, 1 = first interior row) at position s2 of edge e.
