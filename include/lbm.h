@@ -273,6 +273,32 @@ lbm_status lbm_step_multi(const lbm_params *p, lbm_state *s, int64_t n, int leve
                           const double *r_next, void *const *records, int record_planes,
                           void *stream);
 
+/* `count` time steps, level n -> n+count, by the launches that are fastest on this grid: whole
+ * groups of levels per launch where a kernel for them applies (walls included), pairs and
+ * single steps else.  The state, the u* accumulator, the records and the fault bits are those
+ * of `count` calls of lbm_step, bit for bit on every node (padding nodes of the tiled arrays
+ * may receive unspecified values, which no entry point reads).  Flips s->cur once per launch.
+ *   r: host array of count + 1 body-force factors r(n) ... r(n+count).  With s->body_prev set
+ *     every step is one lbm_step with that field; otherwise s->body (or b0) is the field of
+ *     every level.
+ *   edges: host array of `count` boundary data, those at t^{n+1/2} ... ; may be NULL only when
+ *     all edges are periodic (LBM_ERR_ARG otherwise).  On a grid with walls s->aux must hold
+ *     lbm_aux_bytes().
+ *   records: NULL, or a host array of `count` device pointers that receive U^{n+1} ...
+ *     (lbm_record_bytes() each); NULL entries are left out.
+ *   record_planes: with records, 6 writes whole records; 4 allows the velocity planes (0, 1)
+ *     to be left as they were (the adjoint reads only planes 2 .. 5).
+ *   s->ustar may be NULL: the quadrature is then skipped. */
+lbm_status lbm_advance(const lbm_params *p, lbm_state *s, int64_t n, int64_t count, const double *r,
+                       const lbm_edge_data *edges, void *const *records, int record_planes,
+                       void *stream);
+
+/* Levels of the first launch that lbm_advance would make for `left` remaining steps with these
+ * records (NULL, or `left` pointers); 0 on invalid arguments.  A caller that lends a buffer as
+ * the current level advances by this much first: that launch reads the buffer, and a second
+ * one in the same call would write it. */
+int lbm_advance_levels(const lbm_params *p, const lbm_state *s, int64_t left, void *const *records);
+
 /* Displacement at the current level n (eq:trapezoid-u): u^n = u*^{n+1} - (dt/2) v^n with
  * v^n recovered from the stored post-collision populations (sum_q f* = U + (dt/2) B).
  *   r_n: body-force factor at level n.  u_out: device, 2 double planes. */

@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -453,6 +454,183 @@ lbm_status lbm_step_multi(const lbm_params* p, lbm_state* s, int64_t n, int leve
     if (!march_geometry(p, levels, a.nspan, a.seg, a.nwg, a.d_nspan)) return LBM_ERR_UNSUPPORTED;
     if (launch_march(a, (hipStream_t)stream) != hipSuccess) return LBM_ERR_LAUNCH;
     s->cur = 1 - s->cur;
+    return LBM_OK;
+}
+
+}  // extern "C"
+
+// ---------------------------------------------------------------- several steps per call
+
+namespace {
+
+// Geometry of a patch launch: levels per launch and the nodes of a patch.
+struct PatchPlan {
+    int levels, pw, ph;
+};
+
+// The plan by grid size (nodes up to side^2), or levels = 0 where the other kernels are faster.
+// Every line is the fastest of a sweep over 2 .. 8 levels and patches of 4 x 4 to 64 x 8 nodes
+// on square grids (log-NH, uniform parameters).  A small grid wants many levels per launch (a
+// launch costs about 4 us before it computes) and patches small enough to reach every compute
+// unit; from about 400^2 on the arithmetic of the halo costs more than the launches, so levels
+// drop and patches grow.  Measured us per level, patches against the pairs, single steps and
+// multi-level launches they replace:
+//   FP32 periodic  64^2 1.7 / 2.8, 256^2 2.4 / 2.9, 512^2 5.2 / 8.3, 1024^2 14.6 / 17.4, and
+//                  1448^2 42 / 28 (march_kernel from 1150^2 on)
+//   FP32 walls     64^2 5.1 / 10.8, 256^2 6.3 / 10.6, 512^2 8.5 / 18.4, 1024^2 22.5 / 32.9,
+//                  1250^2 49 / 44 (two traction-free edges periodic instead: 48 / 37)
+//   FP64 periodic  64^2 2.0 / 3.8, 256^2 3.5 / 4.1, 700^2 15.4 / 22.8, 1024^2 48 / 43; with
+//                  records 850^2 slower by 3 to 11 %
+//   FP64 walls     64^2 9.4 / 13.9, 256^2 9.6 / 15.4, 700^2 22.6 / 39.8, 1024^2 62 / 60
+// (the traction solves of a wall node, some 700 dependent instructions per level, bound the
+// small walled grids).
+PatchPlan patch_plan(const lbm_params* p, int64_t left) {
+    struct Line {
+        int side, levels, pw, ph;
+    };
+    static const Line kShifted[] = {{80, 8, 8, 4},    {176, 6, 8, 8},   {224, 6, 12, 12}, {330, 6, 32, 8},
+                                    {450, 4, 32, 12}, {600, 3, 32, 16}, {1150, 3, 32, 8}};
+    static const Line kShiftedWalls[] = {{72, 8, 8, 4},   {160, 8, 8, 8},  {224, 6, 12, 12},
+                                         {330, 6, 16, 8}, {450, 4, 16, 16}, {1040, 3, 12, 12}};
+    static const Line kPlain[] = {{80, 8, 4, 4}, {176, 6, 8, 8}, {224, 6, 12, 12}, {330, 4, 16, 16}, {800, 3, 16, 8}};
+    static const Line kPlainWalls[] = {{72, 8, 4, 4}, {176, 8, 8, 8}, {224, 6, 12, 12}, {330, 4, 12, 12}, {800, 3, 16, 8}};
+    const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN;
+    const Line* l = plain ? (walls ? kPlainWalls : kPlain) : (walls ? kShiftedWalls : kShifted);
+    const int lines = plain ? 5 : walls ? 6 : 7;
+    const int64_t nodes = int64_t(p->nx) * p->ny;
+    for (int i = 0; i < lines; ++i, ++l) {
+        if (nodes > int64_t(l->side) * l->side) continue;
+        return PatchPlan{int(std::min<int64_t>(l->levels, left)), std::min(l->pw, p->nx), std::min(l->ph, p->ny)};
+    }
+    return PatchPlan{0, 0, 0};
+}
+
+enum Route { kRouteStep, kRoutePair, kRouteMulti, kRoutePatch };
+
+// The launch that takes the next of `left` steps, and its levels (records: as lbm_advance's,
+// from the next step on, or NULL).
+Route advance_route(const lbm_params* p, const lbm_state* s, int64_t left, void* const* records, PatchPlan& pl) {
+    pl = PatchPlan{1, 0, 0};
+    if (s->body_prev) return kRouteStep;
+    const PatchPlan patch = patch_plan(p, left);
+    if (patch.levels) {
+        pl = patch;
+        return kRoutePatch;
+    }
+    const int64_t nodes = int64_t(p->nx) * p->ny;
+    const bool walls = any_wall(p);
+    if (left >= 2 && !walls && p->storage != LBM_F64_PLAIN) {
+        // march_kernel: without records from 1024^2 on (4 levels, or what is left without
+        // leaving a single step over), with a record of every level from 2048^2 on
+        int levels = int(std::min<int64_t>(kMarchMaxLevels, left)), recs = 0;
+        for (int t = 0; records && t < levels; ++t) recs += records[t] != nullptr;
+        if (recs == 0 && s->ustar && nodes >= 1024 * 1024) {
+            pl.levels = left - levels == 1 && levels > 2 ? levels - 1 : levels;
+            return kRouteMulti;
+        }
+        if (recs == kMarchMaxLevels && !s->ustar && nodes >= 2048 * 2048) {
+            pl.levels = levels;
+            return kRouteMulti;
+        }
+    }
+    if (left >= 2 && (!walls || nodes >= 416 * 416)) {
+        pl.levels = 2;
+        return kRoutePair;
+    }
+    return kRouteStep;
+}
+
+lbm_status patch_launch(const lbm_params* p, lbm_state* s, int64_t n, const PatchPlan& pl, const double* r,
+                        const lbm_edge_data* edges, void* const* records, int record_planes, hipStream_t hs) {
+    PatchArgs a{};
+    a.cm = make_common(p, s);
+    a.cm.body_prev = nullptr;
+    a.src = s->pop[s->cur];
+    a.dst = s->pop[1 - s->cur];
+    a.ustar = s->ustar;
+    a.levels = pl.levels;
+    a.rec_planes = record_planes;
+    for (int t = 0; t <= pl.levels; ++t) {
+        a.r[t] = r[t];
+        for (int k = 0; k < 2; ++k) a.fb[t][k] = float(r[t] * a.cm.b0[k]);
+    }
+    for (int t = 0; t < pl.levels; ++t) {
+        if ((n + 1 + t) % kUstarBlock == 0) a.fold = t + 1;
+        a.rec[t] = records ? records[t] : nullptr;
+        if (!edges) continue;
+        for (int e = 0; e < 4; ++e) {
+            for (int k = 0; k < 2; ++k) a.value[t][e][k] = edges[t].value[e][k];
+            a.field[t][e] = edges[t].field[e];
+        }
+    }
+    // the patches along walls first: their traction solves take longer
+    auto add = [&](int x0, int y0, int x1, int y1) {
+        if (x0 >= x1 || y0 >= y1) return;
+        PatchRect& pr = a.rect[a.nrect++];
+        pr.x0 = x0;
+        pr.y0 = y0;
+        pr.x1 = x1;
+        pr.y1 = y1;
+        pr.pw = pl.pw;
+        pr.ph = pl.ph;
+        pr.first = a.nwg;
+        pr.npx = (x1 - x0 + pl.pw - 1) / pl.pw;
+        pr.d_npx = fast_div(pr.npx);
+        a.nwg += pr.npx * ((y1 - y0 + pl.ph - 1) / pl.ph);
+    };
+    const int pw = pl.pw, ph = pl.ph;
+    const int x1 = a.cm.periodic_x ? 0 : std::min(pw, p->nx), y1 = a.cm.periodic_y ? 0 : std::min(ph, p->ny);
+    const int x2 = a.cm.periodic_x ? p->nx : std::max(x1, p->nx / pw * pw);
+    const int y2 = a.cm.periodic_y ? p->ny : std::max(y1, p->ny / ph * ph);
+    add(0, 0, p->nx, y1);
+    add(0, y2, p->nx, p->ny);
+    add(0, y1, x1, y2);
+    add(x2, y1, p->nx, y2);
+    add(x1, y1, x2, y2);
+    if (launch_patch(a, hs) != hipSuccess) return LBM_ERR_LAUNCH;
+    s->cur = 1 - s->cur;
+    return LBM_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int lbm_advance_levels(const lbm_params* p, const lbm_state* s, int64_t left, void* const* records) {
+    if (lbm_check_params(p) != LBM_OK || !s || left < 1) return 0;
+    PatchPlan pl;
+    advance_route(p, s, left, records, pl);
+    return pl.levels;
+}
+
+lbm_status lbm_advance(const lbm_params* p, lbm_state* s, int64_t n, int64_t count, const double* r,
+                       const lbm_edge_data* edges, void* const* records, int record_planes, void* stream) {
+    lbm_status st = lbm_check_params(p);
+    if (st != LBM_OK) return st;
+    if ((st = check_state(p, s, false)) != LBM_OK) return st;
+    if (count < 0 || !r) return LBM_ERR_ARG;
+    if (any_wall(p) && (!edges || !s->aux)) return LBM_ERR_ARG;
+    if (records && record_planes != 6 && record_planes != 4) return LBM_ERR_ARG;
+    for (int64_t i = 0; i < count;) {
+        const int64_t left = count - i;
+        void* const* rec = records ? records + i : nullptr;
+        const lbm_edge_data* ed = edges ? edges + i : nullptr;
+        PatchPlan pl;
+        switch (advance_route(p, s, left, rec, pl)) {
+            case kRoutePatch: st = patch_launch(p, s, n + i, pl, r + i, ed, rec, record_planes, (hipStream_t)stream); break;
+            case kRouteMulti:
+                st = lbm_step_multi(p, s, n + i, pl.levels, r + i + 1, rec && rec[0] ? rec : nullptr, record_planes,
+                                    stream);
+                break;
+            case kRoutePair:
+                st = lbm_step2(p, s, n + i, r[i], r[i + 1], r[i + 2], ed, ed ? ed + 1 : nullptr, rec ? rec[0] : nullptr,
+                               rec ? rec[1] : nullptr, stream);
+                break;
+            default: st = lbm_step(p, s, n + i, r[i], r[i + 1], ed, rec ? rec[0] : nullptr, stream); break;
+        }
+        if (st != LBM_OK) return st;
+        i += pl.levels;
+    }
     return LBM_OK;
 }
 

@@ -251,6 +251,40 @@ struct MarchAdjArgs {
     FastDiv d_nspan;
 };
 
+// Several levels per launch on patches held in LDS (patch_kernel): one node per thread, the
+// patches tile one or more rectangles of the grid.
+constexpr int kPatchLevels = 8;          // most levels per launch
+// most nodes of a patch with its halo: FP64 and the traction solves take more registers than a
+// workgroup of 1024 threads leaves to each
+constexpr int patch_threads(bool plain, bool walls) { return plain || walls ? 512 : 1024; }
+constexpr int kPatchLds = 160 * 1024;    // LDS of a compute unit
+constexpr int kPatchRects = 5;
+
+struct PatchRect {
+    int x0, y0, x1, y1;              // nodes [x0, x1) x [y0, y1)
+    int pw, ph;                      // nodes of a patch
+    int npx, first;                  // patches per row, index of the first one
+    FastDiv d_npx;
+};
+
+struct PatchArgs {
+    Common cm;
+    const void* src;                 // f*^n
+    void* dst;                       // f*^{n+levels}
+    void* ustar;                     // or NULL: no accumulator update
+    int levels;                      // 1 .. kPatchLevels
+    int fold;                        // level t whose step folds the accumulator, or 0
+    int nwg, nrect;                  // workgroups; rectangles, in launch order (the XCD order
+                                     // applies inside the last one)
+    PatchRect rect[kPatchRects];
+    double r[kPatchLevels + 1];      // body factor r(n + t)
+    float fb[kPatchLevels + 1][2];   // uniform body r(n + t) b0 rounded to float
+    void* rec[kPatchLevels];         // records of U^{n+1+t}, or NULL
+    int rec_planes;                  // 6: whole records; 4: the F - I planes 2 .. 5 only
+    double value[kPatchLevels][4][2];            // wall data at t^{n+t+1/2}
+    const double* field[kPatchLevels][4];
+};
+
 struct TractionArgs {
     Common cm;
     const void* pop;                 // f*^n
@@ -350,6 +384,7 @@ struct AdjInitArgs {
 hipError_t launch_step(const StepArgs& a, hipStream_t s);
 hipError_t launch_step2(const Step2Args& a, hipStream_t s);
 hipError_t launch_march(const MarchArgs& a, hipStream_t s);
+hipError_t launch_patch(const PatchArgs& a, hipStream_t s);
 hipError_t launch_march_adjoint(const MarchAdjArgs& a, hipStream_t s);
 hipError_t launch_traction(TractionArgs a, hipStream_t s);   // every traction edge, one launch
 hipError_t launch_moments(const RecoverArgs& a, hipStream_t s);

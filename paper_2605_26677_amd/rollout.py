@@ -397,13 +397,28 @@ def _steps_to_snapshot(sv, cfg, n0, n, ustar=True):
     bit the two single steps).  The snapshot takes over the buffer the last step wrote
     (Solver.detach_current) rather than a copy of it."""
     rec = sv.new_record()
-    if n > n0 and _pairs(sv, cfg):
+    if _auto(cfg):
+        _auto_steps(sv, cfg, n0, n + 1, records=[None] * (n - n0) + [rec], ustar=ustar)
+    elif n > n0 and _pairs(sv, cfg):
         _plain_steps(sv, cfg, n0, n - 1, ustar=ustar)
         _pair(sv, cfg, n - 1, record2=rec, ustar=ustar)
     else:
         _plain_steps(sv, cfg, n0, n, ustar=ustar)
         sv.step(n, cfg.ramp(n), cfg.ramp(n + 1), _edges(cfg, n), record=rec, ustar=ustar)
     return (sv.detach_current(), rec)
+
+
+def _auto(cfg):
+    """Whether the library picks the launches (lbm_advance): unless the configuration forces
+    pairs or turns the multi-level kernels off."""
+    return cfg.pairs is None and cfg.multi is not False
+
+
+def _auto_steps(sv, cfg, n0, n1, records=None, ustar=True, record_planes=6):
+    """Steps n0 .. n1 - 1 by lbm_advance; records: one entry (or None) per step."""
+    edges = None if sv.periodic else [None if cfg.edges is None else cfg.edges(n) for n in range(n0, n1)]
+    sv.steps(n0, [float(cfg.ramp(n)) for n in range(n0, n1 + 1)], edges=edges, records=records, ustar=ustar,
+             record_planes=record_planes)
 
 
 def _pairs(sv, cfg):
@@ -422,6 +437,9 @@ def _plain_steps(sv, cfg, n0, n1, ustar=True):
     so not where u* is skipped; a shorter group where fewer levels remain, and never a
     single level left over where two groups can share the rest) and else in pairs through
     lbm_step2; bit for bit the same result as single steps."""
+    if _auto(cfg):
+        _auto_steps(sv, cfg, n0, n1, ustar=ustar)
+        return
     n = n0
     pairs = _pairs(sv, cfg)
     multi = sv.multi_levels if (pairs and ustar and cfg.multi is not False) else 0
@@ -451,6 +469,9 @@ def _reverse_segment(sv, cfg, adj, start, end, snap, recs):
     snap = _restore(sv, snap)
     recs = [snap[1]] + recs[1:]
     n = start
+    if _auto(cfg):
+        _auto_steps(sv, cfg, start, end - 1, records=recs[1:end - start], ustar=False, record_planes=4)
+        n = end - 1
     pairs = _pairs(sv, cfg)
     rmulti = sv.replay_multi_levels if (pairs and cfg.multi is not False) else 0
     while n < end - 1:

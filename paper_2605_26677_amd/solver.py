@@ -20,6 +20,23 @@ def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def fill_edges(c, values, keep):
+    """Writes the boundary data of one half step (four pairs, device tensors or None) into a
+    zeroed lbm_edge_data; tensors it points to are appended to `keep`."""
+    for e in range(4):
+        v = values[e]
+        if v is None:
+            continue
+        if isinstance(v, torch.Tensor):
+            t = v.to(torch.float64).contiguous()
+            keep.append(t)
+            c.field[e] = t.data_ptr()
+        else:
+            pair = c.value[e]
+            pair[0] = float(v[0])
+            pair[1] = float(v[1])
+
+
 class EdgeData:
     """Boundary data at one half step: per edge either a pair (uniform along the edge) or
     a (2, L) float64 device tensor."""
@@ -27,17 +44,8 @@ class EdgeData:
     def __init__(self, values=None):
         self.c = L.lbm_edge_data()
         self._keep = []
-        for e in range(4):
-            v = None if values is None else values[e]
-            if v is None:
-                continue
-            if isinstance(v, torch.Tensor):
-                t = v.to(torch.float64).contiguous()
-                self._keep.append(t)
-                self.c.field[e] = t.data_ptr()
-            else:
-                self.c.value[e][0] = float(v[0])
-                self.c.value[e][1] = float(v[1])
+        if values is not None:
+            fill_edges(self.c, values, self._keep)
 
 
 def host_matrix(F):
@@ -348,6 +356,49 @@ class Solver:
         finally:
             self.s.ustar = keep
 
+    def steps(self, n, r, edges=None, records=None, ustar=True, record_planes=6):
+        """lbm_advance: levels n -> n + len(r) - 1 by the fastest launches, bit for bit the
+        same as single steps; r holds the body factors r(n), r(n + 1), ..., edges one entry per
+        step (as step takes them) or None on a periodic grid, records one tensor or None per
+        step, or None."""
+        count = len(r) - 1
+        if edges is not None and len(edges) != count:
+            raise ValueError("edges needs one entry per step")
+        if records is not None and len(records) != count:
+            raise ValueError("records needs one entry per step")
+        if count < 1:
+            return
+        ra = (ctypes.c_double * (count + 1))(*r)
+        ea, held = None, []
+        if edges is not None:
+            ea = (L.lbm_edge_data * count)()
+            for i, e in enumerate(edges):
+                if isinstance(e, EdgeData):
+                    ea[i] = e.c
+                elif e is not None:
+                    fill_edges(ea[i], e, held)
+        rec = None
+        if records is not None:
+            rec = (ctypes.c_void_p * count)(*[None if t is None else t.data_ptr() for t in records])
+        keep = self.s.ustar
+        if not ustar:
+            self.s.ustar = None
+        try:
+            done = 0
+            while done < count:
+                at = [None if x is None else ctypes.byref(x, done * ctypes.sizeof(t))
+                      for x, t in ((ra, ctypes.c_double), (ea, L.lbm_edge_data), (rec, ctypes.c_void_p))]
+                k = count - done
+                if self._lent is not None:
+                    # a lent buffer is read by one launch and then handed back
+                    k = int(self.lib.lbm_advance_levels(ctypes.byref(self.p), ctypes.byref(self.s), k, at[2]))
+                L.check(self.lib.lbm_advance(ctypes.byref(self.p), ctypes.byref(self.s), int(n) + done, k, at[0],
+                                             at[1], at[2], int(record_planes), _stream()), "lbm_advance")
+                self._give_back()
+                done += k
+        finally:
+            self.s.ustar = keep
+
     @property
     def multi_levels(self):
         """Levels per lbm_step_multi call where that is the fastest way to advance: periodic
@@ -413,14 +464,25 @@ class Solver:
         ``edges(n)`` (default zero).  With ``graph`` True, whole blocks of ``block`` steps
         whose arguments equal those of the first captured block replay one captured graph
         and the rest run eagerly; this removes the per-step host cost where it dominates.
-        ``graph`` None captures only grids of at most GRAPH_MAX_NODES nodes: on larger ones
-        eager launches already follow each other without a gap, and a graph replay adds a
-        few microseconds between its kernel nodes.  With ``fused`` True the steps go in
+        On grids of more than GRAPH_MAX_NODES nodes eager launches already follow each other
+        without a gap, and a graph replay adds a few microseconds between its kernel nodes;
+        ``graph`` None with ``fused`` given captures only up to that size.  With neither ``fused`` nor ``graph`` given
+        (or ``graph`` False) the steps go through lbm_advance, which picks the fastest launches
+        for the grid and needs no capture: one launch then takes several levels on small grids
+        too.  With ``fused`` True the steps go in
         groups of multi_levels through lbm_step_multi where that applies, else in pairs
         through lbm_step2 (where pairs_ok), with the same result bit for bit; None fuses
         where it is faster (pairs_pay)."""
         ramp = ramp or (lambda n: 1.0)
         edges = edges or (lambda n: None)
+        if fused is None and not graph:
+            end, n = n0 + count, n0
+            while n < end:
+                m = min(end, n + max(16, block))
+                walls = None if self.periodic else [edges(k) for k in range(n, m)]
+                self.steps(n, [float(ramp(k)) for k in range(n, m + 1)], edges=walls)
+                n = m
+            return
         fused = self.pairs_pay if fused is None else (bool(fused) and self.pairs_ok)
         if graph is None:
             graph_on = self.nx * self.ny <= self.GRAPH_MAX_NODES
