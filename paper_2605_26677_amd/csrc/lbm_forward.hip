@@ -251,6 +251,105 @@ __global__ void __launch_bounds__(kBlock) stress_kernel(RecoverArgs a) {
 
 // ---------------------------------------------------------------- diagnostics
 
+// Sums (k < 7), minimum (k = 7) and maxima (k > 7) of the diagnostics.
+__device__ __forceinline__ double diag_join(int k, double m, double o) {
+    return k == 7 ? fmin(m, o) : k >= 8 ? fmax(m, o) : m + o;
+}
+
+// The tree reduction of a workgroup's values of every diagnostic, in column 0 at the end.
+__device__ __forceinline__ void diag_reduce(double (*red)[kBlock]) {
+    __syncthreads();
+    for (int w = kBlock / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w)
+            for (int k = 0; k < LBM_DIAG_COUNT; ++k)
+                red[k][threadIdx.x] = diag_join(k, red[k][threadIdx.x], red[k][threadIdx.x + w]);
+        __syncthreads();
+    }
+}
+
+// Directions of the acoustic-tensor scan (one degree apart).
+constexpr int kScanDirs = 180;
+
+// The larger eigenvalue of Q_ik = n_A C_iAkB n_B (symmetrised) for the direction n.
+template <typename R>
+__device__ __forceinline__ R acoustic_max(const R C[16], R n0, R n1) {
+    const R nn[2] = {n0, n1};
+    R Q[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            R v = R(0);
+#pragma unroll
+            for (int A = 0; A < 2; ++A)
+#pragma unroll
+                for (int B = 0; B < 2; ++B) v += nn[A] * C[8 * i + 4 * A + 2 * k + B] * nn[B];
+            Q[2 * i + k] = v;
+        }
+    const R tr = R(0.5) * (Q[0] + Q[3]);
+    const R dd = R(0.5) * (Q[0] - Q[3]);
+    const R off = R(0.5) * (Q[1] + Q[2]);
+    return tr + sqrt_r(dd * dd + off * off);
+}
+
+// Bounds of a node's scan, in FP32.  With phi = 2 theta the entries of Q are first-order
+// trigonometric polynomials, the larger eigenvalue is T(phi) + sqrt(S(phi)), T of first and S
+// of second order, so 16 samples bound it over all directions: between two samples T and S
+// exceed their chords by at most |T''| h^2/8 and |S''| h^2/8 (h = pi/8), and the square root
+// of a linear S its own chord by (dS)^2 / (32 Smin^(3/2)).  lo is the largest sample, hi the
+// bound (not finite where S may vanish or the state is not finite: no bound).
+template <typename R>
+__device__ __forceinline__ void scan_bounds(const R C[16], float& lo, float& hi) {
+    float z[3][3];                                  // T, (Q00 - Q11)/2, (Q01 + Q10)/2
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        // coefficients of 1, cos phi, sin phi of Q_ik = (C_i0k0 + C_i1k1)/2 + ...
+        auto coef = [&](int i, int k, int j) {
+            const float a = float(C[8 * i + 2 * k]), b = float(C[8 * i + 4 + 2 * k + 1]);
+            const float c = float(C[8 * i + 2 * k + 1]), d = float(C[8 * i + 4 + 2 * k]);
+            return j == 0 ? 0.5f * (a + b) : j == 1 ? 0.5f * (a - b) : 0.5f * (c + d);
+        };
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            z[m][j] = m == 0 ? 0.5f * (coef(0, 0, j) + coef(1, 1, j))
+                    : m == 1 ? 0.5f * (coef(0, 0, j) - coef(1, 1, j)) : 0.5f * (coef(0, 1, j) + coef(1, 0, j));
+    }
+    float p[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};     // S = p0 + p1 cos + p2 sin + p3 cos 2phi + p4 sin 2phi
+#pragma unroll
+    for (int m = 1; m < 3; ++m) {
+        p[0] += z[m][0] * z[m][0] + 0.5f * (z[m][1] * z[m][1] + z[m][2] * z[m][2]);
+        p[1] += 2.0f * z[m][0] * z[m][1];
+        p[2] += 2.0f * z[m][0] * z[m][2];
+        p[3] += 0.5f * (z[m][1] * z[m][1] - z[m][2] * z[m][2]);
+        p[4] += z[m][1] * z[m][2];
+    }
+    constexpr float h = 0.39269908f;
+    const float t12 = __builtin_amdgcn_sqrtf(z[0][1] * z[0][1] + z[0][2] * z[0][2]);
+    const float p12 = __builtin_amdgcn_sqrtf(p[1] * p[1] + p[2] * p[2]);
+    const float p34 = __builtin_amdgcn_sqrtf(p[3] * p[3] + p[4] * p[4]);
+    const float smin = p[0] - p12 - p34;
+    const float eS = (p12 + 4.0f * p34) * (h * h / 8.0f), dS = (p12 + 2.0f * p34) * h;
+    constexpr float cs[16] = {1.0f, 0.92387953f, 0.70710678f, 0.38268343f, 0.0f, -0.38268343f, -0.70710678f, -0.92387953f,
+                              -1.0f, -0.92387953f, -0.70710678f, -0.38268343f, 0.0f, 0.38268343f, 0.70710678f, 0.92387953f};
+    lo = hi = -1e30f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const float c = cs[k], s = cs[(k + 12) & 15], c2 = cs[(2 * k) & 15], s2 = cs[(2 * k + 12) & 15];
+        const float T = z[0][0] + z[0][1] * c + z[0][2] * s;
+        const float S = p[0] + p[1] * c + p[2] * s + p[3] * c2 + p[4] * s2;
+        lo = fmaxf(lo, T + __builtin_amdgcn_sqrtf(fmaxf(S, 0.0f)));
+        hi = fmaxf(hi, T + __builtin_amdgcn_sqrtf(S + eS));
+    }
+    hi += t12 * (h * h / 8.0f) + dS * dS * __builtin_amdgcn_rcpf(32.0f * smin * __builtin_amdgcn_sqrtf(smin));
+    if (!(smin > 1e-6f * p[0])) hi = __builtin_inff();
+}
+
+// One partial row of LBM_DIAG_COUNT values per workgroup.  The direction scan of the acoustic
+// tensor (180 directions, some 10 000 instructions per node) was the whole cost: 4.06 ms of
+// 4096^2 in FP32.  Only nodes that can hold the workgroup's largest value take it now: those
+// whose bound (scan_bounds) reaches the largest sample seen so far, less 1e-4 of it, ten times
+// what the FP32 scan's rounding (the drift of its rotated direction) can move.  A wavefront
+// with few such nodes takes them one by one, its lanes sharing the directions.
 template <int ST, int LAW, bool FIELDS>
 __global__ void __launch_bounds__(kBlock) diag_kernel(RecoverArgs a) {
     using Tr = Storage<ST>;
@@ -259,98 +358,104 @@ __global__ void __launch_bounds__(kBlock) diag_kernel(RecoverArgs a) {
     constexpr bool SH = Tr::shifted;
     const Common& cm = a.cm;
     const int64_t n = int64_t(cm.nx) * cm.ny;
-    double acc[LBM_DIAG_COUNT];
-    for (int k = 0; k < LBM_DIAG_COUNT; ++k) acc[k] = 0.0;
-    acc[7] = 1e300;
-    acc[8] = 0.0;
-    acc[9] = 0.0;
-    const double hdt = 0.5 * cm.dt;
-    // 1-degree rotation for the direction scan of the acoustic tensor
-    const R cd = R(0.99984769515639123916), sd = R(0.017452406437283512820);
-    for (int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; idx < n;
-         idx += int64_t(gridDim.x) * blockDim.x) {
-        const int y = int(idx / cm.nx), x = int(idx - int64_t(y) * cm.nx);
-        double b0, b1;
-        body_at<FIELDS>(cm, (int)idx, n, a.r_n, b0, b1);
-        R U[6];
-        recover_node<T, R>((const T*)a.pop, cm.ntile, x, y, R(hdt * b0), R(hdt * b1), U);
-        R mu, lam;
-        params_at<FIELDS, R>(cm, (int)idx, mu, lam);
-        R ft[4] = {U[2], U[3], U[4], U[5]};
-        if (!SH) { ft[0] -= R(1); ft[3] -= R(1); }
-        acc[0] += double(U[0]);
-        acc[1] += double(U[1]);
-        for (int k = 0; k < 4; ++k) acc[2 + k] += double(ft[k]);
-        const R W = energy<R, LAW, true>(ft, mu, lam, law_consts<R>(cm));
-        acc[6] += double(R(0.5) * (U[0] * U[0] + U[1] * U[1]) + W);
-        const R J = R(1) + ft[0] + ft[3] + (ft[0] * ft[3] - ft[1] * ft[2]);
-        acc[7] = fmin(acc[7], double(J));
-        acc[8] = fmax(acc[8], double(sqrt_r(ft[0] * ft[0] + ft[1] * ft[1] + ft[2] * ft[2] + ft[3] * ft[3])));
-        R C[16];
-        tangent<R, LAW, true>(ft, mu, lam, law_consts<R>(cm), C);
-        R cs = R(1), sn = R(0), best = R(0);
-        for (int t = 0; t < 180; ++t) {
-            const R nn[2] = {cs, sn};
-            R Q[4];
-            for (int i = 0; i < 2; ++i)
-                for (int k = 0; k < 2; ++k) {
-                    R v = R(0);
-                    for (int A = 0; A < 2; ++A)
-                        for (int B = 0; B < 2; ++B) v += nn[A] * C[8 * i + 4 * A + 2 * k + B] * nn[B];
-                    Q[2 * i + k] = v;
-                }
-            const R tr = R(0.5) * (Q[0] + Q[3]);
-            const R dd = R(0.5) * (Q[0] - Q[3]);
-            const R off = R(0.5) * (Q[1] + Q[2]);
-            const R lmax = tr + sqrt_r(dd * dd + off * off);
-            best = best > lmax ? best : lmax;
+    __shared__ R dirs[2][kScanDirs];
+    __shared__ int floor_bits;                      // the largest sample, as the bits of a float >= 0
+    __shared__ double red[LBM_DIAG_COUNT][kBlock];
+    if (threadIdx.x == 0) {
+        floor_bits = 0;
+        // 1-degree rotation for the direction scan of the acoustic tensor
+        const R cd = R(0.99984769515639123916), sd = R(0.017452406437283512820);
+        R cs = R(1), sn = R(0);
+        for (int t = 0; t < kScanDirs; ++t) {
+            dirs[0][t] = cs;
+            dirs[1][t] = sn;
             const R c2 = cs * cd - sn * sd;
             sn = sn * cd + cs * sd;
             cs = c2;
         }
-        acc[9] = fmax(acc[9], double(sqrt_r(best)) / cm.c);
+    }
+    __syncthreads();
+    double acc[LBM_DIAG_COUNT];
+#pragma unroll
+    for (int k = 0; k < LBM_DIAG_COUNT; ++k) acc[k] = 0.0;
+    acc[7] = 1e300;
+    const double hdt = 0.5 * cm.dt;
+    const int lane = threadIdx.x & (kTile - 1);
+    for (int64_t base = int64_t(blockIdx.x) * blockDim.x; base < n; base += int64_t(gridDim.x) * blockDim.x) {
+        const int64_t idx = base + threadIdx.x;
+        const bool valid = idx < n;
+        R C[16];
+        float lo = 0.0f, hi = -1.0f;
+        if (valid) {
+            const int y = int(idx) / cm.nx, x = int(idx) - y * cm.nx;
+            double b0, b1;
+            body_at<FIELDS>(cm, (int)idx, n, a.r_n, b0, b1);
+            R U[6];
+            recover_node<T, R>((const T*)a.pop, cm.ntile, x, y, R(hdt * b0), R(hdt * b1), U);
+            R mu, lam;
+            params_at<FIELDS, R>(cm, (int)idx, mu, lam);
+            R ft[4] = {U[2], U[3], U[4], U[5]};
+            if (!SH) { ft[0] -= R(1); ft[3] -= R(1); }
+            acc[0] += double(U[0]);
+            acc[1] += double(U[1]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[2 + k] += double(ft[k]);
+            const R W = energy<R, LAW, true>(ft, mu, lam, law_consts<R>(cm));
+            acc[6] += double(R(0.5) * (U[0] * U[0] + U[1] * U[1]) + W);
+            const R J = R(1) + ft[0] + ft[3] + (ft[0] * ft[3] - ft[1] * ft[2]);
+            acc[7] = fmin(acc[7], double(J));
+            acc[8] = fmax(acc[8], double(sqrt_r(ft[0] * ft[0] + ft[1] * ft[1] + ft[2] * ft[2] + ft[3] * ft[3])));
+            tangent<R, LAW, true>(ft, mu, lam, law_consts<R>(cm), C);
+            scan_bounds<R>(C, lo, hi);
+            // one update per wavefront where a lane raises the floor
+            if (isfinite(lo) && lo > 0.0f && __float_as_int(lo) > *(volatile int*)&floor_bits)
+                atomicMax(&floor_bits, __float_as_int(lo));
+        }
+        if (base == int64_t(blockIdx.x) * blockDim.x) __syncthreads();
+        const float thr = __int_as_float(*(volatile int*)&floor_bits) * (1.0f - 1e-4f);
+        const bool odd = valid && !isfinite(hi);
+        const uint64_t want = __ballot(valid && !(hi < thr));
+        if (__ballot(odd) != 0 || __popcll(want) > 40) {
+            if (valid && !(hi < thr)) {
+                R best = R(0);
+                for (int t = 0; t < kScanDirs; ++t) {
+                    const R lmax = acoustic_max<R>(C, dirs[0][t], dirs[1][t]);
+                    best = best > lmax ? best : lmax;
+                }
+                acc[9] = fmax(acc[9], double(sqrt_r(best)) / cm.c);
+            }
+        } else {
+            for (uint64_t m = want; m != 0; m &= m - 1) {
+                const int src = __ffsll((unsigned long long)m) - 1;
+                R D[16];
+                for (int k = 0; k < 16; ++k) D[k] = __shfl(C[k], src);
+                R best = R(0);
+                for (int t = lane; t < kScanDirs; t += kTile) {
+                    const R lmax = acoustic_max<R>(D, dirs[0][t], dirs[1][t]);
+                    best = best > lmax ? best : lmax;
+                }
+                // each lane keeps the largest of its own directions (the square root is monotone)
+                acc[9] = fmax(acc[9], double(sqrt_r(best)) / cm.c);
+            }
+        }
     }
     acc[6] *= cm.dx * cm.dx;
     // block reduction in FP64
-    __shared__ double red[kBlock];
     double* part = (double*)a.scratch + int64_t(blockIdx.x) * LBM_DIAG_COUNT;
-    for (int k = 0; k < LBM_DIAG_COUNT; ++k) {
-        red[threadIdx.x] = acc[k];
-        __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) {
-                const double o = red[threadIdx.x + w];
-                double& m = red[threadIdx.x];
-                m = (k == 7) ? fmin(m, o) : (k >= 8 ? fmax(m, o) : m + o);
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) part[k] = red[0];
-        __syncthreads();
-    }
+    for (int k = 0; k < LBM_DIAG_COUNT; ++k) red[k][threadIdx.x] = acc[k];
+    diag_reduce(red);
+    if (threadIdx.x < LBM_DIAG_COUNT) part[threadIdx.x] = red[threadIdx.x][0];
 }
 
 __global__ void __launch_bounds__(kBlock) diag_final_kernel(const double* part, int nblocks, double* out) {
-    __shared__ double red[kBlock];
+    __shared__ double red[LBM_DIAG_COUNT][kBlock];
     for (int k = 0; k < LBM_DIAG_COUNT; ++k) {
         double m = (k == 7) ? 1e300 : 0.0;
-        for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-            const double o = part[b * LBM_DIAG_COUNT + k];
-            m = (k == 7) ? fmin(m, o) : (k >= 8 ? fmax(m, o) : m + o);
-        }
-        red[threadIdx.x] = m;
-        __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) {
-                const double o = red[threadIdx.x + w];
-                double& r = red[threadIdx.x];
-                r = (k == 7) ? fmin(r, o) : (k >= 8 ? fmax(r, o) : r + o);
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out[k] = red[0];
-        __syncthreads();
+        for (int b = threadIdx.x; b < nblocks; b += blockDim.x) m = diag_join(k, m, part[b * LBM_DIAG_COUNT + k]);
+        red[k][threadIdx.x] = m;
     }
+    diag_reduce(red);
+    if (threadIdx.x < LBM_DIAG_COUNT) out[threadIdx.x] = red[threadIdx.x][0];
 }
 
 // ---------------------------------------------------------------- initialisation
@@ -382,7 +487,12 @@ __global__ void __launch_bounds__(kBlock) init_state_kernel(InitArgs a) {
 
 // Second-order populations (eq:init-compact with eq:init-Zq-components, eq:init-deltaPq,
 // eq:init-expanded) in FP64 shifted form, then the first collision (level 0) and u*^1.
-template <int ST, int LAW, bool FIELDS>
+//
+// REST (no initial displacement and F = I): U0 = (v0, 0), so the kernel reads v0 itself and
+// needs no pass that forms U0.  The general form keeps 30 loads of U0 and its neighbours and
+// the tangent in flight at two wavefronts per SIMD and was bound by their latency: 8192^2 FP32
+// 6.6 ms and 0.75 ms for U0.
+template <int ST, int LAW, bool FIELDS, bool REST>
 __global__ void __launch_bounds__(kBlock) init_pop_kernel(InitArgs a) {
     using Tr = Storage<ST>;
     using T = typename Tr::pop_t;
@@ -390,17 +500,22 @@ __global__ void __launch_bounds__(kBlock) init_pop_kernel(InitArgs a) {
     const Common& cm = a.cm;
     const int nx = cm.nx, ny = cm.ny;
     const int64_t n = int64_t(nx) * ny;
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= n) return;
-    const int y = int(idx / nx), x = int(idx - int64_t(y) * nx);
-    const double* U0p = (const double*)a.scratch;
+    int x, y;
+    if (!tile_thread(nx, ny, cm.ntile, x, y)) return;
+    const int64_t idx = int64_t(y) * nx + x;
+    const double* U0p = REST ? a.v0 : (const double*)a.scratch;
     const double c = cm.c, dt = cm.dt, hdt = 0.5 * cm.dt;
     const double inv2h = 1.0 / (2.0 * cm.dx);
     double U0[6], dX[6], dY[6];
+#pragma unroll
     for (int k = 0; k < 6; ++k) {
+        if (REST && k >= 2) {
+            U0[k] = dX[k] = dY[k] = 0.0;
+            continue;
+        }
         const double* pl = U0p + k * n;
         U0[k] = pl[idx];
-        if (a.dUdX) {
+        if (!REST && a.dUdX) {
             dX[k] = a.dUdX[k * n + idx];
             dY[k] = a.dUdY[k * n + idx];
         } else {
@@ -661,21 +776,27 @@ hipError_t launch_diagnostics(const RecoverArgs& a, hipStream_t s) {
 }
 
 template <int ST, int LAW>
-static void init_st_law(const InitArgs& a, hipStream_t s, dim3 grid) {
+static void init_st_law(const InitArgs& a, hipStream_t s) {
     const bool fields = a.cm.mu || a.cm.lam || a.cm.body;
-    if (fields) hipLaunchKernelGGL((init_pop_kernel<ST, LAW, true>), grid, dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL((init_pop_kernel<ST, LAW, false>), grid, dim3(kBlock), 0, s, a);
+    const dim3 grid(unsigned((int64_t(a.cm.ntile) * a.cm.ny + kBlock / kTile - 1) / (kBlock / kTile)));
+    if (a.rest) {
+        if (fields) hipLaunchKernelGGL((init_pop_kernel<ST, LAW, true, true>), grid, dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((init_pop_kernel<ST, LAW, false, true>), grid, dim3(kBlock), 0, s, a);
+    } else {
+        if (fields) hipLaunchKernelGGL((init_pop_kernel<ST, LAW, true, false>), grid, dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((init_pop_kernel<ST, LAW, false, false>), grid, dim3(kBlock), 0, s, a);
+    }
 }
 
 template <int ST>
-static void init_st(const InitArgs& a, hipStream_t s, dim3 grid) {
+static void init_st(const InitArgs& a, hipStream_t s) {
     switch (a.cm.material) {
-        case LBM_LOGNH: init_st_law<ST, LBM_LOGNH>(a, s, grid); break;
-        case LBM_NH: init_st_law<ST, LBM_NH>(a, s, grid); break;
-        case LBM_MR: init_st_law<ST, LBM_MR>(a, s, grid); break;
-        case LBM_YEOH: init_st_law<ST, LBM_YEOH>(a, s, grid); break;
-        case LBM_GENT: init_st_law<ST, LBM_GENT>(a, s, grid); break;
-        default: init_st_law<ST, LBM_SVK>(a, s, grid); break;
+        case LBM_LOGNH: init_st_law<ST, LBM_LOGNH>(a, s); break;
+        case LBM_NH: init_st_law<ST, LBM_NH>(a, s); break;
+        case LBM_MR: init_st_law<ST, LBM_MR>(a, s); break;
+        case LBM_YEOH: init_st_law<ST, LBM_YEOH>(a, s); break;
+        case LBM_GENT: init_st_law<ST, LBM_GENT>(a, s); break;
+        default: init_st_law<ST, LBM_SVK>(a, s); break;
     }
 }
 
@@ -686,18 +807,21 @@ hipError_t launch_init_state(const InitArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_init(const InitArgs& a, hipStream_t s) {
-    const dim3 grid(nblocks(int64_t(a.cm.nx) * a.cm.ny));
-    hipLaunchKernelGGL(init_state_kernel, grid, dim3(kBlock), 0, s, a);
-    return launch_init_given(a, s);
+    InitArgs b = a;
+    b.rest = !a.u0 && a.Fbar[0] == 1.0 && a.Fbar[1] == 0.0 && a.Fbar[2] == 0.0 && a.Fbar[3] == 1.0;
+    if (!b.rest) {
+        const dim3 grid(nblocks(int64_t(a.cm.nx) * a.cm.ny));
+        hipLaunchKernelGGL(init_state_kernel, grid, dim3(kBlock), 0, s, b);
+    }
+    return launch_init_given(b, s);
 }
 
 // The populations from U0 already in a.scratch (and its derivatives, if given).
 hipError_t launch_init_given(const InitArgs& a, hipStream_t s) {
-    const dim3 grid(nblocks(int64_t(a.cm.nx) * a.cm.ny));
     switch (a.cm.storage) {
-        case LBM_F32_SHIFTED: init_st<LBM_F32_SHIFTED>(a, s, grid); break;
-        case LBM_F16_SHIFTED: init_st<LBM_F16_SHIFTED>(a, s, grid); break;
-        default: init_st<LBM_F64_PLAIN>(a, s, grid); break;
+        case LBM_F32_SHIFTED: init_st<LBM_F32_SHIFTED>(a, s); break;
+        case LBM_F16_SHIFTED: init_st<LBM_F16_SHIFTED>(a, s); break;
+        default: init_st<LBM_F64_PLAIN>(a, s); break;
     }
     return hipGetLastError();
 }

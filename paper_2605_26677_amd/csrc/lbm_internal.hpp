@@ -311,6 +311,7 @@ struct InitArgs {
     const double* u0;
     double Fbar[4];                  // uniform predeformation (I when none is given)
     double r0;
+    int rest;                        // no u0 and Fbar = I: U0 = (v0, 0), scratch is not used
     void* scratch;                   // U0 as 6 double planes (stride n)
     void* dst;                       // f*^0
     void* ustar;

@@ -558,11 +558,13 @@ class Solver:
     def stress(self, r_n=1.0):
         """(P (2, 2, ny, nx), sigma (2, 2, ny, nx)) in FP64 at the current level."""
         P = torch.empty((4, self.ny, self.nx), dtype=torch.float64, device=self.device)
-        S = torch.empty((3, self.ny, self.nx), dtype=torch.float64, device=self.device)
+        # the library writes s11, s12, s22 as planes 0, 1, 2; s22 and the second s12 move on
+        S = torch.empty((4, self.ny, self.nx), dtype=torch.float64, device=self.device)
         L.check(self.lib.lbm_stress(ctypes.byref(self.p), ctypes.byref(self.s), float(r_n), _ptr(P), _ptr(S),
                                     _stream()), "lbm_stress")
-        sig = torch.stack([S[0], S[1], S[1], S[2]])
-        return P.view(2, 2, self.ny, self.nx), sig.view(2, 2, self.ny, self.nx)
+        S[3].copy_(S[2])
+        S[2].copy_(S[1])
+        return P.view(2, 2, self.ny, self.nx), S.view(2, 2, self.ny, self.nx)
 
     def record_state(self, r_n, out):
         L.check(self.lib.lbm_record_state(ctypes.byref(self.p), ctypes.byref(self.s), float(r_n), _ptr(out),
