@@ -443,6 +443,22 @@ lbm_status lbm_adjoint_step_multi(const lbm_params *p, const lbm_state *fwd, lbm
                                   int64_t m, int levels, const double *r, const void *const *records,
                                   const uint64_t *mask, const double *field, void *stream);
 
+/* `count` adjoint levels, m, m - 1, ..., m - count + 1, by the launches that are fastest on this
+ * grid: whole groups of levels per launch where a kernel for them applies (walls included),
+ * pairs and single steps else.  The result, the block sums and the FP64 gradients are those of
+ * `count` calls of lbm_adjoint_step with the same probe table set in a (a->probe_mask and
+ * a->probe_field; without one every level is a single step), bit for bit on every node.  Flips
+ * a->cur once per launch.  Requires count - 1 <= m <= a->nsteps.
+ *   r: host array of `count` body factors r(m), r(m - 1), ...
+ *   edges: host array of `count` boundary data, those at t^{m+1/2}, t^{m-1/2}, ...; may be NULL
+ *     only when all edges are periodic (LBM_ERR_ARG otherwise).  On a grid with walls a->aux
+ *     must hold lbm_aux_bytes().
+ *   records: host array of `count` device pointers, U^m, U^{m-1}, ... as lbm_adjoint_step reads
+ *     them. */
+lbm_status lbm_adjoint_advance(const lbm_params *p, const lbm_state *fwd, lbm_adj_state *a, int64_t m,
+                               int64_t count, const double *r, const lbm_edge_data *edges,
+                               const void *const *records, void *stream);
+
 /* Adjoint of lbm_init: from lambda^0 = dL/df(0) in a->adj[a->cur], writes dL/dv0 into
  * g_v0 (device, 2 double planes; includes the direct term of u*^0 = u0 - (dt/2) v0) and
  * adds the initialisation parts of dL/dmu, dL/dlam, dL/db.  v0, u0, Fbar, r0 as given to

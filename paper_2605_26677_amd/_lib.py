@@ -94,6 +94,8 @@ SIGNATURES = {
     "lbm_diagnostics_noalloc": (c_i32, [P(lbm_params), P(lbm_state), c_dbl, c_vp, c_vp]),
     "lbm_adjoint_step": (c_i32, [P(lbm_params), P(lbm_state), P(lbm_adj_state), c_i64, c_dbl,
                                  P(lbm_edge_data), c_vp, c_vp]),
+    "lbm_adjoint_advance": (c_i32, [P(lbm_params), P(lbm_state), P(lbm_adj_state), c_i64, c_i64, c_vp, c_vp, c_vp,
+                                    c_vp]),
     "lbm_adjoint_init": (c_i32, [P(lbm_params), P(lbm_state), P(lbm_adj_state), c_vp, c_vp, c_vp,
                                  c_dbl, c_vp, c_vp]),
     "lbm_record_state": (c_i32, [P(lbm_params), P(lbm_state), c_dbl, c_vp, c_vp]),

@@ -17,14 +17,6 @@
 
 namespace lbm {
 
-template <typename R>
-__device__ __forceinline__ R D_sign(int bc, int k) {
-    // velocity rule diag(-1,-1,1,1,1,1), traction rule diag(1,1,-1,-1,-1,-1)
-    const bool vrow = k < 2;
-    if (bc == LBM_VELOCITY) return vrow ? R(-1) : R(1);
-    return vrow ? R(1) : R(-1);
-}
-
 template <int ST, int LAW, bool WALLS, bool FIELDS>
 __global__ void __launch_bounds__(kBlock) adjoint_kernel(AdjArgs a) {
     using R = typename Storage<ST>::real;
@@ -115,12 +107,8 @@ __global__ void __launch_bounds__(kBlock) adjoint_kernel(AdjArgs a) {
     }
 }
 
-// Traction edges, stage 1 (one thread per wall link): F^b is rebuilt from the record of
-// U^m as the forward step builds it (tangential column = the wall node's own, normal
-// column by the Newton solve), then dL/dF^b = lambda^{m+1}_d(X0)_F / 2 is carried through
-// the solve by the implicit function theorem: with y = J^{-T} (dL/da), the tangential
-// column receives -N_A y_i C_iAjB and mu, lam receive -N_A y_i dP_iA/dp.  One launch
-// covers every traction edge, one wavefront per workgroup.  Each link stages
+// Traction edges, stage 1 (one thread per wall link): the link's terms (adj_link) with
+// dL/dF^b = lambda^{m+1}_d(X0)_F / 2.  One launch covers every traction edge, one wavefront per workgroup.  Each link stages
 // (tbar_1, tbar_2, dL/dmu, dL/dlam) in its own slot of the staging buffer; they reach
 // lambda^m and the gradients in the scatter stage, which gives a corner node the terms of
 // its edges in edge order.
@@ -130,25 +118,14 @@ __device__ __forceinline__ void adj_traction_solve(const AdjArgs& a, int e) {
     const Common& cm = a.cm;
     const EdgeGeom G = edge_geom(e);
     const int L = (A == 0) ? cm.ny : cm.nx;
-    constexpr int Bx = 1 - A;
     const int s = (int(blockIdx.x) - a.eblk[e]) * kTracWin + int(threadIdx.x);
     if (s >= L) return;
     const XY n0 = edge_node(G, cm.nx, cm.ny, 0, s);
     const R* rec = (const R*)a.record + tile_base(cm.ntile, 6, n0.x, n0.y);
-    R tang[2], acol[2], Tv[2];
-    for (int k = 0; k < 2; ++k) {
-        tang[k] = rec[(2 + 2 * k + Bx) * kTile];
-        acol[k] = rec[(2 + 2 * k + A) * kTile];
-        Tv[k] = edge_value<R>(a.ed, e, k, s, L);
-    }
-    const int id0 = n0.y * cm.nx + n0.x;
-    R mu, lam;
-    params_at<FIELDS, R>(cm, id0, mu, lam);
-    newton_column<R, LAW, true, A>(R(G.NA), tang, Tv, mu, lam, law_consts<R>(cm), acol, cm.newton_max_iter,
-                                   R(cm.newton_tol));
-    R f[4];
-    f[A] = acol[0]; f[2 + A] = acol[1];
-    f[Bx] = tang[0]; f[2 + Bx] = tang[1];
+    R ft[4], mu, lam;
+    for (int k = 0; k < 4; ++k) ft[k] = rec[(2 + k) * kTile];
+    const R Tv[2] = {edge_value<R>(a.ed, e, 0, s, L), edge_value<R>(a.ed, e, 1, s, L)};
+    params_at<FIELDS, R>(cm, n0.y * cm.nx + n0.x, mu, lam);
     // dL/dF^b = lambda^{m+1}_d(X0)_F / 2: from the populations, or (the second level of a
     // two-level step) from the wall line of the staging buffer
     R Fbar[4];
@@ -160,31 +137,10 @@ __device__ __forceinline__ void adj_traction_solve(const AdjArgs& a, int e) {
         const int64_t wb = tile_base(cm.ntile, 24, n0.x, n0.y);
         for (int k = 0; k < 4; ++k) Fbar[k] = R(0.5) * src[wb + (6 * G.d + 2 + k) * kTile];
     }
-    R C[16];
-    tangent<R, LAW, true>(f, mu, lam, law_consts<R>(cm), C);
-    const R NA = R(G.NA);
-    const R j00 = NA * C[4 * A + A], j01 = NA * C[4 * A + 2 + A];
-    const R j10 = NA * C[8 + 4 * A + A], j11 = NA * C[8 + 4 * A + 2 + A];
-    const R det = j00 * j11 - j01 * j10;
-    const R ab0 = Fbar[A], ab1 = Fbar[2 + A];
-    // y = J^{-T} abar
-    const R y0 = (j11 * ab0 - j10 * ab1) / det;
-    const R y1 = (-j01 * ab0 + j00 * ab1) / det;
-    R tbar[2];
-    for (int jj = 0; jj < 2; ++jj)
-        tbar[jj] = Fbar[2 * jj + Bx] - NA * (y0 * C[4 * A + 2 * jj + Bx] + y1 * C[8 + 4 * A + 2 * jj + Bx]);
-    R gm = R(0), gl = R(0);
-    if (a.g_mu || a.g_lam) {
-        R Pm[4], Pl[4];
-        piola_partials<R, LAW, true>(f, law_consts<R>(cm), Pm, Pl);
-        gm = -NA * (y0 * Pm[A] + y1 * Pm[2 + A]);
-        gl = -NA * (y0 * Pl[A] + y1 * Pl[2 + A]);
-    }
+    R t[4];
+    adj_link<R, LAW, A>(cm, R(G.NA), ft, Tv, Fbar, mu, lam, a.g_mu || a.g_lam, t);
     R* aux = (R*)a.aux + 4 * (int64_t)(edge_off(cm.nx, cm.ny, e) + s);
-    aux[0] = tbar[0];
-    aux[1] = tbar[1];
-    aux[2] = gm;
-    aux[3] = gl;
+    for (int k = 0; k < 4; ++k) aux[k] = t[k];
 }
 
 // The edge's normal axis is a template parameter of the solve (fixed per edge, so per

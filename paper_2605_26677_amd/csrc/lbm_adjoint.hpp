@@ -104,6 +104,55 @@ __device__ __forceinline__ void adj_node(const Common& cm, const R l[4][6], cons
     }
 }
 
+template <typename R>
+__device__ __forceinline__ R D_sign(int bc, int k) {
+    // velocity rule diag(-1,-1,1,1,1,1), traction rule diag(1,1,-1,-1,-1,-1)
+    const bool vrow = k < 2;
+    if (bc == LBM_VELOCITY) return vrow ? R(-1) : R(1);
+    return vrow ? R(1) : R(-1);
+}
+
+// The adjoint of one traction link: F^b is rebuilt from the record ft of U^m at the wall node
+// as the forward step builds it (tangential column = the node's own, normal column by the
+// Newton solve), then Fbar = dL/dF^b is carried through the solve by the implicit function
+// theorem: with y = J^{-T} (dL/da), the tangential column receives -N_A y_i C_iAjB and mu, lam
+// receive -N_A y_i dP_iA/dp.  t: (tbar_1, tbar_2, dL/dmu, dL/dlam).
+template <typename R, int LAW, int A>
+__device__ __forceinline__ void adj_link(const Common& cm, R NA, const R ft[4], const R Tv[2], const R Fbar[4], R mu,
+                                         R lam, bool grad_par, R t[4]) {
+    constexpr int Bx = 1 - A;
+    R tang[2], acol[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        tang[k] = ft[2 * k + Bx];
+        acol[k] = ft[2 * k + A];
+    }
+    newton_column<R, LAW, true, A>(NA, tang, Tv, mu, lam, law_consts<R>(cm), acol, cm.newton_max_iter,
+                                   R(cm.newton_tol));
+    R f[4];
+    f[A] = acol[0]; f[2 + A] = acol[1];
+    f[Bx] = tang[0]; f[2 + Bx] = tang[1];
+    R C[16];
+    tangent<R, LAW, true>(f, mu, lam, law_consts<R>(cm), C);
+    const R j00 = NA * C[4 * A + A], j01 = NA * C[4 * A + 2 + A];
+    const R j10 = NA * C[8 + 4 * A + A], j11 = NA * C[8 + 4 * A + 2 + A];
+    const R det = j00 * j11 - j01 * j10;
+    const R ab0 = Fbar[A], ab1 = Fbar[2 + A];
+    // y = J^{-T} abar
+    const R y0 = (j11 * ab0 - j10 * ab1) / det;
+    const R y1 = (-j01 * ab0 + j00 * ab1) / det;
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+        t[jj] = Fbar[2 * jj + Bx] - NA * (y0 * C[4 * A + 2 * jj + Bx] + y1 * C[8 + 4 * A + 2 * jj + Bx]);
+    t[2] = t[3] = R(0);
+    if (grad_par) {
+        R Pm[4], Pl[4];
+        piola_partials<R, LAW, true>(f, law_consts<R>(cm), Pm, Pl);
+        t[2] = -NA * (y0 * Pm[A] + y1 * Pm[2 + A]);
+        t[3] = -NA * (y0 * Pl[A] + y1 * Pl[2 + A]);
+    }
+}
+
 // Probe source of the level at node (x, y) if it is a probe (bit x mod 64 of the word of
 // its tile row in the probe table): lambda_q += weight ubar for every q (the sum of the
 // ubar of every probe on that cell).  Without a table the probes are walked by

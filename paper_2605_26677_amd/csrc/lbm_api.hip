@@ -126,6 +126,18 @@ lbm_status check_state(const lbm_params* p, const lbm_state* s, bool need_ustar 
     return LBM_OK;
 }
 
+// Compute units of the current device, queried once per device (256 on an MI355X).
+int compute_units() {
+    static std::atomic<int> cached[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int v = cached[dev].load(std::memory_order_relaxed);
+    if (v > 0) return v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
+    cached[dev].store(v, std::memory_order_relaxed);
+    return v;
+}
+
 lbm_status launched(hipError_t e) { return e == hipSuccess ? LBM_OK : LBM_ERR_LAUNCH; }
 
 // Uniform predeformation: I when none is given; rejected unless finite with det > 0.
@@ -384,18 +396,6 @@ lbm_status lbm_step2(const lbm_params* p, lbm_state* s, int64_t n, double r_n, d
     return LBM_OK;
 }
 
-// Compute units of the current device, queried once per device (256 on an MI355X).
-static int compute_units() {
-    static std::atomic<int> cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int v = cached[dev].load(std::memory_order_relaxed);
-    if (v > 0) return v;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-    cached[dev].store(v, std::memory_order_relaxed);
-    return v;
-}
-
 // Workgroups of the multi-level kernels: spans of kMarchTiles tiles per row, segments of
 // `seg` rows.  A segment repeats 2 (levels - 1) rows of the first level and fewer of the
 // later ones, and the launch runs in rounds of one workgroup per compute unit: the length
@@ -468,53 +468,103 @@ struct PatchPlan {
     int levels, pw, ph;
 };
 
-// The plan by grid size (nodes up to side^2), or levels = 0 where the other kernels are faster.
-// Every line is the fastest of a sweep over 2 .. 8 levels and patches of 4 x 4 to 64 x 8 nodes
-// on square grids (log-NH, uniform parameters).  A small grid wants many levels per launch (a
-// launch costs about 4 us before it computes) and patches small enough to reach every compute
-// unit; from about 400^2 on the arithmetic of the halo costs more than the launches, so levels
-// drop and patches grow.  Measured us per level, patches against the pairs, single steps and
-// multi-level launches they replace:
+bool invariant_material(const lbm_params* p) {
+    return p->material == LBM_MR || p->material == LBM_YEOH || p->material == LBM_GENT;
+}
+
+// What a patch launch costs, in arbitrary units (only the choice between plans uses it):
+// `launch` once; every further round of patches on a compute unit, `round`; and per level and
+// round the larger of `level` (one node's chain of dependent instructions and the barrier, with
+// walls the traction solves before it) and `wave` for every wavefront of the level, of which
+// patches of one compute unit beyond the first add the share `share` (they fill each other's
+// waits).  `waves` wavefronts fit a compute unit.  Fitted to sweeps over 2 .. 8 levels and
+// patches of 4 x 4 to 32 x 16 nodes on 18 grids of 64 x 64 to 1024 x 1024 nodes (log-NH and Gent):
+// the chosen plan is 4 % slower than the best of the sweep on average (FP64 with walls 11 %).  Patches are
+// used up to `side`^2 nodes.
+struct PatchCost {
+    double launch, level, wave, round, share;
+    int side, threads, waves;
+};
+
+// Levels per launch and patch with the least cost per level, or levels = 0 beyond c.side^2.
+PatchPlan patch_choice(const lbm_params* p, const PatchCost& c, int words, bool links) {
+    static const int kLevels[] = {2, 3, 4, 6, 8};
+    static const int kShapes[][2] = {{4, 4},   {8, 4},   {8, 8},   {12, 8}, {12, 12}, {16, 8},
+                                     {16, 12}, {16, 16}, {20, 16}, {32, 8}, {32, 12}, {32, 16}};
+    PatchPlan best{0, 0, 0};
+    if (int64_t(p->nx) * p->ny > int64_t(c.side) * c.side) return best;
+    double least = 0.0;
+    const int cus = compute_units(), size = int(real_size(p));
+    for (const auto& sh : kShapes) {
+        const int pw = std::min(sh[0], p->nx), ph = std::min(sh[1], p->ny);
+        const int64_t nwg = int64_t((p->nx + pw - 1) / pw) * ((p->ny + ph - 1) / ph);
+        const int per_cu = int((nwg + cus - 1) / cus);
+        for (const int T : kLevels) {
+            const int nodes = (pw + 2 * (T - 1)) * (ph + 2 * (T - 1));
+            const int lds = (nodes * words + (links ? 8 * (pw + ph + 4 * (T - 1)) : 0)) * size;
+            if (nodes > c.threads || lds > kPatchLds) break;
+            const int at_once = std::max(1, std::min(kPatchLds / lds, c.waves / ((nodes + kTile - 1) / kTile)));
+            const int rounds = (per_cu + at_once - 1) / at_once;
+            double t = c.launch + (rounds - 1) * c.round;
+            for (int k = 0; k < T; ++k)
+                t += std::max(c.level * rounds, c.wave * ((per_cu - 1) * c.share + 1.0) *
+                                                    (((pw + 2 * k) * (ph + 2 * k) + kTile - 1) / kTile));
+            // rows of 32 nodes read and write whole cache lines (256^2 FP32, 6 levels: 2.39 us
+            // per level at 32 x 8, 2.66 at 16 x 16)
+            if (pw >= 32) t *= 0.92;
+            if (best.levels == 0 || t / T < least) {
+                least = t / T;
+                best = PatchPlan{T, pw, ph};
+            }
+        }
+    }
+    return best;
+}
+
+// The plan of patch_kernel.  Where it stops (side) the other kernels are faster.  Measured us
+// per level, patches against the pairs, single steps and multi-level launches they replace
+// (log-NH, uniform parameters):
 //   FP32 periodic  64^2 1.7 / 2.8, 256^2 2.4 / 2.9, 512^2 5.2 / 8.3, 1024^2 14.6 / 17.4, and
 //                  1448^2 42 / 28 (march_kernel from 1150^2 on)
 //   FP32 walls     64^2 5.1 / 10.8, 256^2 6.3 / 10.6, 512^2 8.5 / 18.4, 1024^2 22.5 / 32.9,
 //                  1250^2 49 / 44 (two traction-free edges periodic instead: 48 / 37)
 //   FP64 periodic  64^2 2.0 / 3.8, 256^2 3.5 / 4.1, 700^2 15.4 / 22.8, 1024^2 48 / 43; with
-//                  records 850^2 slower by 3 to 11 %
-//   FP64 walls     64^2 9.4 / 13.9, 256^2 9.6 / 15.4, 700^2 22.6 / 39.8, 1024^2 62 / 60
+//                  records 600^2 13.8 / 18.5, 850^2 41 / 38
+//   FP64 walls     64^2 9.4 / 13.9, 256^2 9.6 / 15.4, 700^2 22.6 / 39.8, 1024^2 62 / 60; between
+//                  two velocity walls with records 512^2 17 / 23, 850^2 56 / 46
 // (the traction solves of a wall node, some 700 dependent instructions per level, bound the
 // small walled grids).
-PatchPlan patch_plan(const lbm_params* p, int64_t left) {
-    struct Line {
-        int side, levels, pw, ph;
-    };
-    static const Line kShifted[] = {{80, 8, 8, 4},    {176, 6, 8, 8},   {224, 6, 12, 12}, {330, 6, 32, 8},
-                                    {450, 4, 32, 12}, {600, 3, 32, 16}, {1150, 3, 32, 8}};
-    static const Line kShiftedWalls[] = {{72, 8, 8, 4},   {160, 8, 8, 8},  {224, 6, 12, 12},
-                                         {330, 6, 16, 8}, {450, 4, 16, 16}, {1040, 3, 12, 12}};
-    static const Line kPlain[] = {{80, 8, 4, 4}, {176, 6, 8, 8}, {224, 6, 12, 12}, {330, 4, 16, 16}, {800, 3, 16, 8}};
-    static const Line kPlainWalls[] = {{72, 8, 4, 4}, {176, 8, 8, 8}, {224, 6, 12, 12}, {330, 4, 12, 12}, {800, 3, 16, 8}};
-    const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN;
-    const Line* l = plain ? (walls ? kPlainWalls : kPlain) : (walls ? kShiftedWalls : kShifted);
-    const int lines = plain ? 5 : walls ? 6 : 7;
+PatchPlan patch_plan(const lbm_params* p) {
+    static const PatchCost kShifted{12.7, 0.84, 0.457, 3.43, 1.0, 1150, patch_threads(false, false), 24};
+    static const PatchCost kShiftedWalls{18.4, 1.37, 0.090, 3.58, 0.57, 1040, patch_threads(false, true), 24};
+    static const PatchCost kPlain{7.71, 8.22, 1.31, 3.42, 0.96, 750, patch_threads(true, false), 12};
+    static const PatchCost kPlainWalls{7.40, 2.22, 0.341, 3.28, 0.79, 700, patch_threads(true, true), 12};
+    const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN, half = p->storage == LBM_F16_SHIFTED;
     const int64_t nodes = int64_t(p->nx) * p->ny;
-    for (int i = 0; i < lines; ++i, ++l) {
-        if (nodes > int64_t(l->side) * l->side) continue;
-        return PatchPlan{int(std::min<int64_t>(l->levels, left)), std::min(l->pw, p->nx), std::min(l->ph, p->ny)};
-    }
-    return PatchPlan{0, 0, 0};
+    // FP16 pairs move half the bytes: they win where their grids fit the caches (638 x 339: 4.3
+    // us per level, patches 5.4; 404^2 and 584^2 are 3 and 17 % slower in pairs), and on large
+    // grids without traction edges (756 x 1095 4 %)
+    if (half && !walls && nodes > 430 * 430 && nodes < 530 * 530) return PatchPlan{0, 0, 0};
+    if (half && walls && !has_traction(p) && nodes > 860 * 860) return PatchPlan{0, 0, 0};
+    // large grids: many rounds of small workgroups, three to a compute unit (1000 x 777: 11.8 us
+    // per level, 13.9 with the least-cost plan)
+    if (!plain && !walls && nodes > 720 * 720 && nodes <= int64_t(kShifted.side) * kShifted.side && p->nx >= 32)
+        return PatchPlan{3, 32, std::min(8, p->ny)};
+    return patch_choice(p, plain ? (walls ? kPlainWalls : kPlain) : (walls ? kShiftedWalls : kShifted),
+                        walls ? 27 : 25, false);
 }
 
 enum Route { kRouteStep, kRoutePair, kRouteMulti, kRoutePatch };
 
 // The launch that takes the next of `left` steps, and its levels (records: as lbm_advance's,
-// from the next step on, or NULL).
-Route advance_route(const lbm_params* p, const lbm_state* s, int64_t left, void* const* records, PatchPlan& pl) {
+// from the next step on, or NULL; patch: patch_plan).
+Route advance_route(const lbm_params* p, const lbm_state* s, const PatchPlan& patch, int64_t left,
+                    void* const* records, PatchPlan& pl) {
     pl = PatchPlan{1, 0, 0};
     if (s->body_prev) return kRouteStep;
-    const PatchPlan patch = patch_plan(p, left);
     if (patch.levels) {
         pl = patch;
+        pl.levels = int(std::min<int64_t>(patch.levels, left));
         return kRoutePatch;
     }
     const int64_t nodes = int64_t(p->nx) * p->ny;
@@ -540,6 +590,36 @@ Route advance_route(const lbm_params* p, const lbm_state* s, int64_t left, void*
     return kRouteStep;
 }
 
+// The patches of the whole grid, those along walls first (their traction solves take longer).
+PatchMap patch_map(const lbm_params* p, const PatchPlan& pl) {
+    PatchMap m{};
+    m.pw = pl.pw;
+    m.ph = pl.ph;
+    auto add = [&](int x0, int y0, int x1, int y1) {
+        if (x0 >= x1 || y0 >= y1) return;
+        PatchRect& pr = m.rect[m.nrect++];
+        pr.x0 = x0;
+        pr.y0 = y0;
+        pr.x1 = x1;
+        pr.y1 = y1;
+        pr.first = m.nwg;
+        pr.npx = (x1 - x0 + pl.pw - 1) / pl.pw;
+        pr.d_npx = fast_div(pr.npx);
+        m.nwg += pr.npx * ((y1 - y0 + pl.ph - 1) / pl.ph);
+    };
+    const bool perx = p->bc[LBM_XMIN] == LBM_PERIODIC, pery = p->bc[LBM_YMIN] == LBM_PERIODIC;
+    const int pw = pl.pw, ph = pl.ph;
+    const int x1 = perx ? 0 : std::min(pw, p->nx), y1 = pery ? 0 : std::min(ph, p->ny);
+    const int x2 = perx ? p->nx : std::max(x1, p->nx / pw * pw);
+    const int y2 = pery ? p->ny : std::max(y1, p->ny / ph * ph);
+    add(0, 0, p->nx, y1);
+    add(0, y2, p->nx, p->ny);
+    add(0, y1, x1, y2);
+    add(x2, y1, p->nx, y2);
+    add(x1, y1, x2, y2);
+    return m;
+}
+
 lbm_status patch_launch(const lbm_params* p, lbm_state* s, int64_t n, const PatchPlan& pl, const double* r,
                         const lbm_edge_data* edges, void* const* records, int record_planes, hipStream_t hs) {
     PatchArgs a{};
@@ -563,32 +643,69 @@ lbm_status patch_launch(const lbm_params* p, lbm_state* s, int64_t n, const Patc
             a.field[t][e] = edges[t].field[e];
         }
     }
-    // the patches along walls first: their traction solves take longer
-    auto add = [&](int x0, int y0, int x1, int y1) {
-        if (x0 >= x1 || y0 >= y1) return;
-        PatchRect& pr = a.rect[a.nrect++];
-        pr.x0 = x0;
-        pr.y0 = y0;
-        pr.x1 = x1;
-        pr.y1 = y1;
-        pr.pw = pl.pw;
-        pr.ph = pl.ph;
-        pr.first = a.nwg;
-        pr.npx = (x1 - x0 + pl.pw - 1) / pl.pw;
-        pr.d_npx = fast_div(pr.npx);
-        a.nwg += pr.npx * ((y1 - y0 + pl.ph - 1) / pl.ph);
-    };
-    const int pw = pl.pw, ph = pl.ph;
-    const int x1 = a.cm.periodic_x ? 0 : std::min(pw, p->nx), y1 = a.cm.periodic_y ? 0 : std::min(ph, p->ny);
-    const int x2 = a.cm.periodic_x ? p->nx : std::max(x1, p->nx / pw * pw);
-    const int y2 = a.cm.periodic_y ? p->ny : std::max(y1, p->ny / ph * ph);
-    add(0, 0, p->nx, y1);
-    add(0, y2, p->nx, p->ny);
-    add(0, y1, x1, y2);
-    add(x2, y1, p->nx, y2);
-    add(x1, y1, x2, y2);
+    a.map = patch_map(p, pl);
     if (launch_patch(a, hs) != hipSuccess) return LBM_ERR_LAUNCH;
     s->cur = 1 - s->cur;
+    return LBM_OK;
+}
+
+// The plan of patch_adj_kernel (us per level, patches against the pairs and single steps,
+// per-node mu and lam, gradients of mu, lam and b):
+//   FP32 periodic  128^2 2.6 / 3.6, 256^2 3.4 / 3.7, 512^2 7.6 / 9.9, 850^2 18.4 / 23.0,
+//                  1024^2 32 / 29
+//   FP32 walls     128^2 5.0 / 18.1, 256^2 5.9 / 22.4, 512^2 10.2 / 26.6, 1024^2 37 / 48,
+//                  1448^2 74 / 82 (between two velocity walls 1050^2 37.5 / 39.9, 1448^2 72 / 70)
+//   FP64 periodic  64^2 2.6 / 4.9, 256^2 4.5 / 6.0, 512^2 11.9 / 17.5, 1024^2 62 / 60
+//   FP64 walls     64^2 6.8 / 22.1, 256^2 9.0 / 28.4, 700^2 38 / 51, 1024^2 86 / 82 (between two
+//                  velocity walls 512^2 18 / 27, 850^2 61 / 55)
+// The invariant-based laws differentiate their stress in forward mode, whose registers leave
+// fewer wavefronts; their halo work costs more (Gent, FP32 periodic: 512^2 13.0 / 14.8,
+// 1024^2 47 / 43; walls 512^2 16.4 / 35.7, 1024^2 57 / 65; FP64 256^2 8.2 / 8.4, 512^2 29 / 30,
+// walls 512^2 39 / 53, 1024^2 154 / 134).
+PatchPlan patch_adj_plan(const lbm_params* p) {
+    static const PatchCost kShifted{24.6, 2.20, 0.585, 67.3, 0.83, 900, kPatchAdjThreads, 24};
+    static const PatchCost kShiftedWalls{2.92, 0.78, 0.081, 11.0, 0.86, 1300, kPatchAdjThreads, 24};
+    static const PatchCost kPlain{13.6, 0.96, 0.121, 1.46, 0.70, 800, kPatchAdjThreads, 12};
+    static const PatchCost kPlainWalls{2.01, 5.73, 0.732, 1.65, 1.0, 780, kPatchAdjThreads, 12};
+    static const PatchCost kInvShifted{3.18, 4.20, 0.808, 0.66, 0.54, 920, kPatchAdjThreads, 24};
+    static const PatchCost kInvShiftedWalls{3.09, 37.5, 4.19, 6.26, 0.55, 1030, kPatchAdjThreads, 24};
+    static const PatchCost kInvPlain{10.8, 20.7, 2.81, 1.91, 0.90, 420, kPatchAdjThreads, 12};
+    static const PatchCost kInvPlainWalls{3.77, 13.0, 1.50, 2.38, 1.0, 700, kPatchAdjThreads, 12};
+    const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN;
+    const PatchCost& c = invariant_material(p)
+                             ? (plain ? (walls ? kInvPlainWalls : kInvPlain) : (walls ? kInvShiftedWalls : kInvShifted))
+                             : (plain ? (walls ? kPlainWalls : kPlain) : (walls ? kShiftedWalls : kShifted));
+    return patch_choice(p, c, 25, walls);
+}
+
+lbm_status patch_adj_launch(const lbm_params* p, const lbm_state* fwd, lbm_adj_state* adj, int64_t m,
+                            const PatchPlan& pl, const double* r, const lbm_edge_data* edges,
+                            const void* const* records, hipStream_t hs) {
+    PatchAdjArgs a{};
+    a.cm = make_common(p, fwd);
+    a.src = adj->adj[adj->cur];
+    a.dst = adj->adj[1 - adj->cur];
+    a.levels = pl.levels;
+    a.map = patch_map(p, pl);
+    for (int t = 0; t < pl.levels; ++t) {
+        if ((m - t) % kGradBlock == 0) a.fold = t + 1;
+        a.rec[t] = records[t];
+        a.r[t] = r[t];
+        if (!edges) continue;
+        for (int e = 0; e < 4; ++e) {
+            for (int k = 0; k < 2; ++k) a.value[t][e][k] = edges[t].value[e][k];
+            a.field[t][e] = edges[t].field[e];
+        }
+    }
+    a.g_mu = adj->g_mu;
+    a.g_lam = adj->g_lam;
+    a.g_body = adj->g_body;
+    a.gsum = adj->gsum;
+    a.pmask = adj->nprobe > 0 ? adj->probe_mask : nullptr;
+    a.pfield = adj->nprobe > 0 ? adj->probe_field : nullptr;
+    a.probe_weight = a.cm.dt;                    // every level of the launch is below N
+    if (launch_patch_adjoint(a, hs) != hipSuccess) return LBM_ERR_LAUNCH;
+    adj->cur = 1 - adj->cur;
     return LBM_OK;
 }
 
@@ -599,7 +716,7 @@ extern "C" {
 int lbm_advance_levels(const lbm_params* p, const lbm_state* s, int64_t left, void* const* records) {
     if (lbm_check_params(p) != LBM_OK || !s || left < 1) return 0;
     PatchPlan pl;
-    advance_route(p, s, left, records, pl);
+    advance_route(p, s, patch_plan(p), left, records, pl);
     return pl.levels;
 }
 
@@ -611,12 +728,13 @@ lbm_status lbm_advance(const lbm_params* p, lbm_state* s, int64_t n, int64_t cou
     if (count < 0 || !r) return LBM_ERR_ARG;
     if (any_wall(p) && (!edges || !s->aux)) return LBM_ERR_ARG;
     if (records && record_planes != 6 && record_planes != 4) return LBM_ERR_ARG;
+    const PatchPlan patch = patch_plan(p);
     for (int64_t i = 0; i < count;) {
         const int64_t left = count - i;
         void* const* rec = records ? records + i : nullptr;
         const lbm_edge_data* ed = edges ? edges + i : nullptr;
         PatchPlan pl;
-        switch (advance_route(p, s, left, rec, pl)) {
+        switch (advance_route(p, s, patch, left, rec, pl)) {
             case kRoutePatch: st = patch_launch(p, s, n + i, pl, r + i, ed, rec, record_planes, (hipStream_t)stream); break;
             case kRouteMulti:
                 st = lbm_step_multi(p, s, n + i, pl.levels, r + i + 1, rec && rec[0] ? rec : nullptr, record_planes,
@@ -830,6 +948,52 @@ lbm_status lbm_adjoint_step_multi(const lbm_params* p, const lbm_state* fwd, lbm
     if (!march_geometry(p, levels, a.nspan, a.seg, a.nwg, a.d_nspan)) return LBM_ERR_UNSUPPORTED;
     if (launch_march_adjoint(a, (hipStream_t)stream) != hipSuccess) return LBM_ERR_LAUNCH;
     adj->cur = 1 - adj->cur;
+    return LBM_OK;
+}
+
+lbm_status lbm_adjoint_advance(const lbm_params* p, const lbm_state* fwd, lbm_adj_state* adj, int64_t m, int64_t count,
+                               const double* r, const lbm_edge_data* edges, const void* const* records,
+                               void* stream) {
+    lbm_status st = lbm_check_params(p);
+    if (st != LBM_OK) return st;
+    if (!fwd || !adj || !adj->adj[0] || !adj->adj[1] || !r || !records) return LBM_ERR_ARG;
+    if (adj->cur != 0 && adj->cur != 1) return LBM_ERR_ARG;
+    if (adj->nprobe < 0 || (adj->nprobe > 0 && (!adj->probe || !adj->ubar))) return LBM_ERR_ARG;
+    if (count < 0 || m - (count - 1) < 0 || m > adj->nsteps) return LBM_ERR_ARG;
+    for (int64_t i = 0; i < count; ++i)
+        if (!records[i]) return LBM_ERR_ARG;
+    const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN;
+    if (walls && (!edges || !adj->aux)) return LBM_ERR_ARG;
+    if (!plain && (adj->g_mu || adj->g_lam || adj->g_body) && !adj->gsum) return LBM_ERR_ARG;
+    // the kernels of several levels take the probe sources from the probe table
+    const bool table = adj->nprobe == 0 || (adj->probe_mask && adj->probe_field);
+    const PatchPlan plan = patch_adj_plan(p);
+    for (int64_t i = 0; i < count;) {
+        const int64_t left = count - i, lm = m - i;
+        const lbm_edge_data* ed = edges ? edges + i : nullptr;
+        PatchPlan pl = plan;
+        pl.levels = int(std::min<int64_t>(pl.levels, left));
+        const int multi = invariant_material(p) ? 3 : 4;
+        int done = 1;
+        if (!table || lm == adj->nsteps) {
+            st = lbm_adjoint_step(p, fwd, adj, lm, r[i], ed, records[i], stream);
+        } else if (pl.levels) {
+            done = pl.levels;
+            st = patch_adj_launch(p, fwd, adj, lm, pl, r + i, ed, records + i, (hipStream_t)stream);
+        } else if (!walls && !plain && left >= multi && int64_t(p->nx) * p->ny >= 2048 * 2048) {
+            done = multi;
+            st = lbm_adjoint_step_multi(p, fwd, adj, lm, multi, r + i, records + i, adj->probe_mask, adj->probe_field,
+                                        stream);
+        } else if (left >= 2) {
+            done = 2;
+            st = lbm_adjoint_step2(p, fwd, adj, lm, r[i], r[i + 1], ed, ed ? ed + 1 : nullptr, records[i],
+                                   records[i + 1], adj->probe_mask, adj->probe_field, stream);
+        } else {
+            st = lbm_adjoint_step(p, fwd, adj, lm, r[i], ed, records[i], stream);
+        }
+        if (st != LBM_OK) return st;
+        i += done;
+    }
     return LBM_OK;
 }
 

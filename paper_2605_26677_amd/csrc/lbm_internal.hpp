@@ -257,14 +257,21 @@ constexpr int kPatchLevels = 8;          // most levels per launch
 // most nodes of a patch with its halo: FP64 and the traction solves take more registers than a
 // workgroup of 1024 threads leaves to each
 constexpr int patch_threads(bool plain, bool walls) { return plain || walls ? 512 : 1024; }
+constexpr int kPatchAdjThreads = 512;    // the same for the adjoint
 constexpr int kPatchLds = 160 * 1024;    // LDS of a compute unit
 constexpr int kPatchRects = 5;
 
 struct PatchRect {
     int x0, y0, x1, y1;              // nodes [x0, x1) x [y0, y1)
-    int pw, ph;                      // nodes of a patch
     int npx, first;                  // patches per row, index of the first one
     FastDiv d_npx;
+};
+
+struct PatchMap {
+    int pw, ph;                      // nodes of a patch
+    int nwg, nrect;                  // workgroups; rectangles, in launch order (the XCD order
+                                     // applies inside the last one)
+    PatchRect rect[kPatchRects];
 };
 
 struct PatchArgs {
@@ -274,15 +281,34 @@ struct PatchArgs {
     void* ustar;                     // or NULL: no accumulator update
     int levels;                      // 1 .. kPatchLevels
     int fold;                        // level t whose step folds the accumulator, or 0
-    int nwg, nrect;                  // workgroups; rectangles, in launch order (the XCD order
-                                     // applies inside the last one)
-    PatchRect rect[kPatchRects];
+    PatchMap map;
     double r[kPatchLevels + 1];      // body factor r(n + t)
     float fb[kPatchLevels + 1][2];   // uniform body r(n + t) b0 rounded to float
     void* rec[kPatchLevels];         // records of U^{n+1+t}, or NULL
     int rec_planes;                  // 6: whole records; 4: the F - I planes 2 .. 5 only
     double value[kPatchLevels][4][2];            // wall data at t^{n+t+1/2}
     const double* field[kPatchLevels][4];
+};
+
+// Several adjoint levels per launch on the same patches (patch_adj_kernel).
+struct PatchAdjArgs {
+    Common cm;
+    const void* src;                 // lambda^{m+1}
+    void* dst;                       // lambda^{m+1-levels}
+    int levels;
+    int fold;                        // level t that folds the block sums, or 0
+    PatchMap map;
+    const void* rec[kPatchLevels];   // U^{m-t}
+    double r[kPatchLevels];          // body factors r(m - t)
+    double value[kPatchLevels][4][2];            // wall data at t^{m-t+1/2}
+    const double* field[kPatchLevels][4];
+    double* g_mu;
+    double* g_lam;
+    double* g_body;
+    void* gsum;
+    const uint64_t* pmask;           // probe table (lbm_adjoint_probe_table) or NULL
+    const double* pfield;
+    double probe_weight;
 };
 
 struct TractionArgs {
@@ -386,6 +412,7 @@ hipError_t launch_step(const StepArgs& a, hipStream_t s);
 hipError_t launch_step2(const Step2Args& a, hipStream_t s);
 hipError_t launch_march(const MarchArgs& a, hipStream_t s);
 hipError_t launch_patch(const PatchArgs& a, hipStream_t s);
+hipError_t launch_patch_adjoint(const PatchAdjArgs& a, hipStream_t s);
 hipError_t launch_march_adjoint(const MarchAdjArgs& a, hipStream_t s);
 hipError_t launch_traction(TractionArgs a, hipStream_t s);   // every traction edge, one launch
 hipError_t launch_moments(const RecoverArgs& a, hipStream_t s);

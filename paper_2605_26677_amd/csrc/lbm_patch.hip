@@ -13,45 +13,13 @@
 // (patch_plan).  Measured: 64^2 FP64 5.9 -> 1.8 us per level, 256^2 FP32 3.1 -> 2.1, 1024^2
 // FP32 with traction walls 33 -> 21 (the single steps and pairs it replaces, with their traction
 // and wall passes).
-#include <algorithm>
-
 #include "lbm_collide.hpp"
 #include "lbm_device.hpp"
 #include "lbm_internal.hpp"
 #include "lbm_kernel_util.hpp"
+#include "lbm_patch.hpp"
 
 namespace lbm {
-
-// Position of thread i of a patch of pw x ph nodes: the nodes of the patch first, row by row
-// (ring 0), then the rings of nodes at distance 1, 2, ... around it (top row, bottom row, left
-// and right columns), so that the nodes a level still needs are a prefix of the threads and
-// whole wavefronts retire as the halo shrinks.
-struct PatchPos {
-    int x, y, ring;
-};
-__device__ __forceinline__ PatchPos patch_pos(int i, int pw, int ph) {
-    PatchPos p;
-    if (i < pw * ph) {
-        p.y = i / pw;
-        p.x = i - p.y * pw;
-        p.ring = 0;
-        return p;
-    }
-    int k = 1;
-    while (i >= (pw + 2 * k) * (ph + 2 * k)) ++k;
-    const int w = pw + 2 * k, h = ph + 2 * k - 2;
-    const int j = i - (w - 2) * h;
-    p.ring = k;
-    if (j < 2 * w) {
-        p.x = (j < w ? j : j - w) - k;
-        p.y = j < w ? -k : ph - 1 + k;
-    } else {
-        const int c = j - 2 * w;
-        p.x = c < h ? -k : pw - 1 + k;
-        p.y = (c < h ? c : c - h) - k + 1;
-    }
-    return p;
-}
 
 // The missing link of a wall node whose edge's normal lies along axis AX (lo: the edge at
 // coordinate 0, else the one at the far end), at position s of the edge, from the node's own
@@ -97,20 +65,14 @@ __global__ void __launch_bounds__(patch_threads(ST == LBM_F64_PLAIN, WALLS)) pat
     const Common& cm = a.cm;
     const int nx = cm.nx, ny = cm.ny, ntile = cm.ntile, levels = a.levels;
     const int64_t n = int64_t(nx) * ny;
-    int g = blockIdx.x, rc = 0;
-    while (rc + 1 < a.nrect && g >= a.rect[rc + 1].first) ++rc;
-    const PatchRect& pr = a.rect[rc];
-    g -= pr.first;
-    if (rc == a.nrect - 1) g = remap_tile(g, a.nwg - pr.first);
-    const int by = fdiv(g, pr.d_npx), bx = g - by * pr.npx;
-    const int pw = pr.pw, ph = pr.ph;
-    const int px0 = pr.x0 + bx * pw, py0 = pr.y0 + by * ph;
+    int pw, ph, px0, py0, px1, py1;
+    patch_at(a.map, pw, ph, px0, py0, px1, py1);
     const PatchPos pos = patch_pos(threadIdx.x, pw, ph);
     const int X = px0 + pos.x, Y = py0 + pos.y;
     const int rw = pw + 2 * (levels - 1);
     const bool valid = pos.ring < levels && (!WALLS || ((cm.periodic_x || (X >= 0 && X < nx)) &&
                                                         (cm.periodic_y || (Y >= 0 && Y < ny))));
-    const bool core = valid && pos.ring == 0 && X < pr.x1 && Y < pr.y1;
+    const bool core = valid && pos.ring == 0 && X < px1 && Y < py1;
     const int xr = wrap_index(X, nx), yr = wrap_index(Y, ny);
     R* own = sh + ((pos.y + levels - 1) * rw + (pos.x + levels - 1)) * NS;
     // the neighbours a node pulls q0 .. q3 from, and streams q2, q3, q0, q1 to
@@ -370,11 +332,9 @@ template <int ST, int LAW>
 static hipError_t patch_st_law(const PatchArgs& a, hipStream_t s) {
     const bool fields = a.cm.mu || a.cm.lam || a.cm.body;
     const bool walls = !(a.cm.periodic_x && a.cm.periodic_y);
-    int nodes = 0;                               // of the largest patch with its halo
-    for (int i = 0; i < a.nrect; ++i)
-        nodes = std::max(nodes, (a.rect[i].pw + 2 * (a.levels - 1)) * (a.rect[i].ph + 2 * (a.levels - 1)));
+    const int nodes = (a.map.pw + 2 * (a.levels - 1)) * (a.map.ph + 2 * (a.levels - 1));
     const size_t lds = size_t(nodes) * patch_stride(walls && fields) * sizeof(typename Storage<ST>::real);
-    const dim3 grid(unsigned(a.nwg)), block(unsigned((nodes + kTile - 1) / kTile * kTile));
+    const dim3 grid(unsigned(a.map.nwg)), block(unsigned((nodes + kTile - 1) / kTile * kTile));
     if (block.x > unsigned(patch_threads(ST == LBM_F64_PLAIN, walls)) || lds > size_t(kPatchLds)) return hipErrorInvalidValue;
     if (walls) {
         if (fields) hipLaunchKernelGGL((patch_kernel<ST, LAW, true, true>), grid, block, lds, s, a);

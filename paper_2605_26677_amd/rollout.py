@@ -24,7 +24,7 @@ from typing import Callable, Optional, Sequence
 import torch
 
 from . import _lib as L
-from .solver import EdgeData, Solver, _ptr, _stream, host_matrix
+from .solver import EdgeData, Solver, _ptr, _stream, fill_edges, host_matrix
 
 
 @dataclass
@@ -371,6 +371,23 @@ class _Adjoint:
                                               _ptr(self.pfield), _stream()),
                 "lbm_adjoint_step_multi")
 
+    def steps(self, sv, cfg, m, records):
+        """lbm_adjoint_advance: levels m, m - 1, ..., m - len(records) + 1 by the fastest
+        launches; records[t] holds U^{m-t}."""
+        k = len(records)
+        r = (ctypes.c_double * k)(*[float(cfg.ramp(m - t)) for t in range(k)])
+        recs = (ctypes.c_void_p * k)(*[rec.data_ptr() for rec in records])
+        ed, held = None, []
+        if not sv.periodic:
+            ed = (L.lbm_edge_data * k)()
+            if cfg.edges is not None:
+                for t in range(k):
+                    v = cfg.edges(m - t)
+                    if v is not None:
+                        fill_edges(ed[t], v, held)
+        L.check(sv.lib.lbm_adjoint_advance(ctypes.byref(sv.p), ctypes.byref(sv.s), ctypes.byref(self.a), int(m), int(k),
+                                           r, ed, recs, _stream()), "lbm_adjoint_advance")
+
     def init(self, sv, cfg, v0, u0):
         L.check(sv.lib.lbm_adjoint_init(ctypes.byref(sv.p), ctypes.byref(sv.s), ctypes.byref(self.a), _ptr(v0),
                                         _ptr(u0), host_matrix(cfg.Fbar), float(cfg.ramp(0)), _ptr(self.g_v0),
@@ -487,6 +504,9 @@ def _reverse_segment(sv, cfg, adj, start, end, snap, recs):
             sv.step(n, cfg.ramp(n), cfg.ramp(n + 1), _edges(cfg, n), record=recs[n + 1 - start], ustar=False)
             n += 1
     m = end - 1
+    if _auto(cfg):
+        adj.steps(sv, cfg, m, recs[m - start::-1])
+        return
     multi = sv.adj_multi_levels if (cfg.pairs is not False and cfg.multi is not False) else 0
     while m >= start:
         if multi and m - (multi - 1) >= start and m < cfg.nsteps:
