@@ -401,24 +401,52 @@ lbm_status lbm_step2(const lbm_params* p, lbm_state* s, int64_t n, double r_n, d
 // later ones, and the launch runs in rounds of one workgroup per compute unit: the length
 // between 8 and 1024 rows that minimises rounds x iterations per workgroup (8192^2: 205
 // rows in three full rounds; with at most 64 rows, 62 rows in ten rounds ran 4 % slower).
-static bool march_geometry(const lbm_params* p, int levels, int& nspan, int& seg, int& nwg, FastDiv& d_nspan) {
-    const int ntile = (p->nx + kTile - 1) / kTile;
-    nspan = (ntile + kMarchTiles - 1) / kMarchTiles;
+static bool march_geometry(int tiles, int per_span, int rows, int levels, int& nspan, int& seg, int& nwg, FastDiv& d_nspan) {
+    nspan = (tiles + per_span - 1) / per_span;
     const int cus = compute_units();
     int best = 8;
     int64_t best_cost = -1;
     for (int sg = 8; sg <= 1024; ++sg) {
-        const int64_t ns = (p->ny + sg - 1) / sg;
+        const int64_t ns = (rows + sg - 1) / sg;
         const int64_t rounds = (ns * nspan + cus - 1) / cus;
         const int64_t cost = rounds * (sg + 2 * (levels - 1));
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = sg; }
     }
-    seg = best < p->ny ? best : p->ny;
-    const int64_t nseg = (p->ny + seg - 1) / seg;
+    seg = best < rows ? best : rows;
+    const int64_t nseg = (rows + seg - 1) / seg;
     if (nseg * nspan > 0x7fffffff) return false;
     nwg = int(nseg * nspan);
     d_nspan = fast_div(nspan);
     return true;
+}
+
+// The march over tiles [tile0, tile1) of the rows [row0, row1), level n -> n + levels, into the
+// other population buffer (s->cur is not flipped).
+static lbm_status march_launch(const lbm_params* p, const lbm_state* s, int64_t n, int levels, const double* r_next,
+                               void* const* records, int record_planes, int tile0, int tile1, int row0, int row1,
+                               hipStream_t hs) {
+    MarchArgs a{};
+    a.cm = make_common(p, s);
+    a.cm.body_prev = nullptr;
+    a.src = s->pop[s->cur];
+    a.dst = s->pop[1 - s->cur];
+    a.ustar = s->ustar;
+    a.levels = levels;
+    a.rec_planes = records ? record_planes : 6;
+    for (int t = 0; t < levels; ++t) {
+        a.fold[t] = (n + 1 + t) % kUstarBlock == 0;
+        a.rec[t] = records ? records[t] : nullptr;
+        a.r[t] = r_next[t];
+        for (int k = 0; k < 2; ++k) a.fb[t][k] = float(r_next[t] * a.cm.b0[k]);
+    }
+    a.tile0 = tile0;
+    a.tile1 = tile1;
+    a.row0 = row0;
+    a.row1 = row1;
+    if (!march_geometry(tile1 - tile0, march_tiles(p->storage == LBM_F64_PLAIN), row1 - row0, levels, a.nspan, a.seg,
+                        a.nwg, a.d_nspan))
+        return LBM_ERR_UNSUPPORTED;
+    return launched(launch_march(a, hs));
 }
 
 lbm_status lbm_step_multi(const lbm_params* p, lbm_state* s, int64_t n, int levels, const double* r_next,
@@ -437,22 +465,9 @@ lbm_status lbm_step_multi(const lbm_params* p, lbm_state* s, int64_t n, int leve
     if (any_wall(p)) return LBM_ERR_UNSUPPORTED;
     // the replay form: records, no accumulator, shifted storages
     if (records && (s->ustar || p->storage == LBM_F64_PLAIN)) return LBM_ERR_UNSUPPORTED;
-    MarchArgs a{};
-    a.cm = make_common(p, s);
-    a.cm.body_prev = nullptr;
-    a.src = s->pop[s->cur];
-    a.dst = s->pop[1 - s->cur];
-    a.ustar = s->ustar;
-    a.levels = levels;
-    a.rec_planes = records ? record_planes : 6;
-    for (int t = 0; t < levels; ++t) {
-        a.fold[t] = (n + 1 + t) % kUstarBlock == 0;
-        a.rec[t] = records ? records[t] : nullptr;
-        a.r[t] = r_next[t];
-        for (int k = 0; k < 2; ++k) a.fb[t][k] = float(r_next[t] * a.cm.b0[k]);
-    }
-    if (!march_geometry(p, levels, a.nspan, a.seg, a.nwg, a.d_nspan)) return LBM_ERR_UNSUPPORTED;
-    if (launch_march(a, (hipStream_t)stream) != hipSuccess) return LBM_ERR_LAUNCH;
+    st = march_launch(p, s, n, levels, r_next, records, record_planes, 0, (p->nx + kTile - 1) / kTile, 0, p->ny,
+                      (hipStream_t)stream);
+    if (st != LBM_OK) return st;
     s->cur = 1 - s->cur;
     return LBM_OK;
 }
@@ -526,8 +541,8 @@ PatchPlan patch_choice(const lbm_params* p, const PatchCost& c, int words, bool 
 // (log-NH, uniform parameters):
 //   FP32 periodic  64^2 1.7 / 2.8, 256^2 2.4 / 2.9, 512^2 5.2 / 8.3, 1024^2 14.6 / 17.4, and
 //                  1448^2 42 / 28 (march_kernel from 1150^2 on)
-//   FP32 walls     64^2 5.1 / 10.8, 256^2 6.3 / 10.6, 512^2 8.5 / 18.4, 1024^2 22.5 / 32.9,
-//                  1250^2 49 / 44 (two traction-free edges periodic instead: 48 / 37)
+//   FP32 walls     64^2 5.1 / 10.8, 256^2 6.3 / 10.6, 512^2 8.5 / 18.4, 1024^2 22.5 / 32.9
+//                  (from 1100^2 on the march of the inner rectangle, see kRimNodes)
 //   FP64 periodic  64^2 2.0 / 3.8, 256^2 3.5 / 4.1, 700^2 15.4 / 22.8, 1024^2 48 / 43; with
 //                  records 600^2 13.8 / 18.5, 850^2 41 / 38
 //   FP64 walls     64^2 9.4 / 13.9, 256^2 9.6 / 15.4, 700^2 22.6 / 39.8, 1024^2 62 / 60; between
@@ -536,7 +551,7 @@ PatchPlan patch_choice(const lbm_params* p, const PatchCost& c, int words, bool 
 // small walled grids).
 PatchPlan patch_plan(const lbm_params* p) {
     static const PatchCost kShifted{12.7, 0.84, 0.457, 3.43, 1.0, 1150, patch_threads(false, false), 24};
-    static const PatchCost kShiftedWalls{18.4, 1.37, 0.090, 3.58, 0.57, 1040, patch_threads(false, true), 24};
+    static const PatchCost kShiftedWalls{18.4, 1.37, 0.090, 3.58, 0.57, 1100, patch_threads(false, true), 24};
     static const PatchCost kPlain{7.71, 8.22, 1.31, 3.42, 0.96, 750, patch_threads(true, false), 12};
     static const PatchCost kPlainWalls{7.40, 2.22, 0.341, 3.28, 0.79, 700, patch_threads(true, true), 12};
     const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN, half = p->storage == LBM_F16_SHIFTED;
@@ -554,7 +569,13 @@ PatchPlan patch_plan(const lbm_params* p) {
                         walls ? 27 : 25, false);
 }
 
-enum Route { kRouteStep, kRoutePair, kRouteMulti, kRoutePatch };
+enum Route { kRouteStep, kRoutePair, kRouteMulti, kRouteRim, kRoutePatch };
+
+// Nodes from which a grid with walls takes the march of its inner rectangle, without records and
+// with (FP32 log-NH, two traction-free pairs of edges, us per level, march and patches around it
+// against patches alone and pairs: 1050^2 25 / 23 / 34, 1250^2 33 / 49 / 44; 2200^2 73 / - / 120;
+// 4096^2 with per-node mu and lam 0.23 ms / - / 0.43).
+constexpr int64_t kRimNodes = 1100 * 1100, kRimRecNodes = 1100 * 1100;
 
 // The launch that takes the next of `left` steps, and its levels (records: as lbm_advance's,
 // from the next step on, or NULL; patch: patch_plan).
@@ -569,18 +590,26 @@ Route advance_route(const lbm_params* p, const lbm_state* s, const PatchPlan& pa
     }
     const int64_t nodes = int64_t(p->nx) * p->ny;
     const bool walls = any_wall(p);
-    if (left >= 2 && !walls && p->storage != LBM_F64_PLAIN) {
-        // march_kernel: without records from 1024^2 on (4 levels, or what is left without
-        // leaving a single step over), with a record of every level from 2048^2 on
+    if (left >= 2) {
+        // march_kernel: without records (4 levels, or what is left without leaving a single step
+        // over) and, in the shifted storages, with a record of every level; on a grid with walls
+        // its inner rectangle, and the patches the rest
+        const bool f64 = p->storage == LBM_F64_PLAIN;
         int levels = int(std::min<int64_t>(kMarchMaxLevels, left)), recs = 0;
         for (int t = 0; records && t < levels; ++t) recs += records[t] != nullptr;
-        if (recs == 0 && s->ustar && nodes >= 1024 * 1024) {
-            pl.levels = left - levels == 1 && levels > 2 ? levels - 1 : levels;
-            return kRouteMulti;
+        bool go;
+        if (f64) {
+            const int side = invariant_material(p) ? (walls ? 1250 : 1100) : (walls ? 850 : 750);
+            go = recs == 0 && s->ustar && levels > 2 && nodes >= int64_t(side) * side;
+        } else if (recs == 0) {
+            go = s->ustar && nodes >= (walls ? kRimNodes : 1024 * 1024);
+        } else {
+            go = recs == kMarchMaxLevels && !s->ustar && nodes >= (walls ? kRimRecNodes : 2048 * 2048);
         }
-        if (recs == kMarchMaxLevels && !s->ustar && nodes >= 2048 * 2048) {
-            pl.levels = levels;
-            return kRouteMulti;
+        if (go && (!walls || (p->nx >= 4 * kTile && p->ny >= 4 * kTile))) {
+            pl.levels = recs == 0 && left - levels == 1 && levels > 2 ? levels - 1 : levels;
+            pl.pw = pl.ph = 16;
+            return walls ? kRouteRim : kRouteMulti;
         }
     }
     if (left >= 2 && (!walls || nodes >= 416 * 416)) {
@@ -590,8 +619,29 @@ Route advance_route(const lbm_params* p, const lbm_state* s, const PatchPlan& pa
     return kRouteStep;
 }
 
-// The patches of the whole grid, those along walls first (their traction solves take longer).
-PatchMap patch_map(const lbm_params* p, const PatchPlan& pl) {
+// The rectangle of a walled grid that the multi-level kernels take (march_kernel; the patches
+// take the rest): whole tiles and rows at least `levels` nodes away from every wall line.
+struct Inner {
+    int tile0, tile1, row0, row1;
+};
+
+Inner inner_rect(const lbm_params* p, int levels, int ph) {
+    const bool perx = p->bc[LBM_XMIN] == LBM_PERIODIC, pery = p->bc[LBM_YMIN] == LBM_PERIODIC;
+    Inner in{0, (p->nx + kTile - 1) / kTile, 0, p->ny};
+    if (!perx) {
+        in.tile0 = 1;
+        in.tile1 = (p->nx - levels) / kTile;
+    }
+    if (!pery) {
+        in.row0 = ph;
+        in.row1 = p->ny - ph;
+    }
+    return in;
+}
+
+// The patches of the whole grid, those along walls first (their traction solves take longer),
+// or of the grid outside the rectangle `in`.
+PatchMap patch_map(const lbm_params* p, const PatchPlan& pl, const Inner* in = nullptr) {
     PatchMap m{};
     m.pw = pl.pw;
     m.ph = pl.ph;
@@ -609,19 +659,26 @@ PatchMap patch_map(const lbm_params* p, const PatchPlan& pl) {
     };
     const bool perx = p->bc[LBM_XMIN] == LBM_PERIODIC, pery = p->bc[LBM_YMIN] == LBM_PERIODIC;
     const int pw = pl.pw, ph = pl.ph;
-    const int x1 = perx ? 0 : std::min(pw, p->nx), y1 = pery ? 0 : std::min(ph, p->ny);
-    const int x2 = perx ? p->nx : std::max(x1, p->nx / pw * pw);
-    const int y2 = pery ? p->ny : std::max(y1, p->ny / ph * ph);
+    int x1 = perx ? 0 : std::min(pw, p->nx), y1 = pery ? 0 : std::min(ph, p->ny);
+    int x2 = perx ? p->nx : std::max(x1, p->nx / pw * pw);
+    int y2 = pery ? p->ny : std::max(y1, p->ny / ph * ph);
+    if (in) {
+        x1 = in->tile0 * kTile;
+        x2 = std::min(in->tile1 * kTile, p->nx);
+        y1 = in->row0;
+        y2 = in->row1;
+    }
     add(0, 0, p->nx, y1);
     add(0, y2, p->nx, p->ny);
     add(0, y1, x1, y2);
     add(x2, y1, p->nx, y2);
-    add(x1, y1, x2, y2);
+    if (!in) add(x1, y1, x2, y2);
     return m;
 }
 
 lbm_status patch_launch(const lbm_params* p, lbm_state* s, int64_t n, const PatchPlan& pl, const double* r,
-                        const lbm_edge_data* edges, void* const* records, int record_planes, hipStream_t hs) {
+                        const lbm_edge_data* edges, void* const* records, int record_planes, hipStream_t hs,
+                        const Inner* in = nullptr) {
     PatchArgs a{};
     a.cm = make_common(p, s);
     a.cm.body_prev = nullptr;
@@ -643,9 +700,9 @@ lbm_status patch_launch(const lbm_params* p, lbm_state* s, int64_t n, const Patc
             a.field[t][e] = edges[t].field[e];
         }
     }
-    a.map = patch_map(p, pl);
+    a.map = patch_map(p, pl, in);
     if (launch_patch(a, hs) != hipSuccess) return LBM_ERR_LAUNCH;
-    s->cur = 1 - s->cur;
+    if (!in) s->cur = 1 - s->cur;
     return LBM_OK;
 }
 
@@ -736,6 +793,16 @@ lbm_status lbm_advance(const lbm_params* p, lbm_state* s, int64_t n, int64_t cou
         PatchPlan pl;
         switch (advance_route(p, s, patch, left, rec, pl)) {
             case kRoutePatch: st = patch_launch(p, s, n + i, pl, r + i, ed, rec, record_planes, (hipStream_t)stream); break;
+            case kRouteRim: {
+                const Inner in = inner_rect(p, pl.levels, pl.ph);
+                void* const* all = rec && rec[0] ? rec : nullptr;
+                st = patch_launch(p, s, n + i, pl, r + i, ed, all, record_planes, (hipStream_t)stream, &in);
+                if (st == LBM_OK)
+                    st = march_launch(p, s, n + i, pl.levels, r + i + 1, all, record_planes, in.tile0, in.tile1, in.row0,
+                                      in.row1, (hipStream_t)stream);
+                if (st == LBM_OK) s->cur = 1 - s->cur;
+                break;
+            }
             case kRouteMulti:
                 st = lbm_step_multi(p, s, n + i, pl.levels, r + i + 1, rec && rec[0] ? rec : nullptr, record_planes,
                                     stream);
@@ -945,7 +1012,8 @@ lbm_status lbm_adjoint_step_multi(const lbm_params* p, const lbm_state* fwd, lbm
     a.pfield = adj->nprobe > 0 ? field : nullptr;
     a.probe_weight = a.cm.dt;                    // every level of the pass is below N
     a.levels = levels;
-    if (!march_geometry(p, levels, a.nspan, a.seg, a.nwg, a.d_nspan)) return LBM_ERR_UNSUPPORTED;
+    if (!march_geometry((p->nx + kTile - 1) / kTile, kMarchTiles, p->ny, levels, a.nspan, a.seg, a.nwg, a.d_nspan))
+        return LBM_ERR_UNSUPPORTED;
     if (launch_march_adjoint(a, (hipStream_t)stream) != hipSuccess) return LBM_ERR_LAUNCH;
     adj->cur = 1 - adj->cur;
     return LBM_OK;

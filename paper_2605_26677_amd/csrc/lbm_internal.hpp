@@ -214,6 +214,12 @@ constexpr int kMarchMaxLevels = 4;
 constexpr int kMarchWaves = 8;
 constexpr int kMarchTiles = 7;
 constexpr int kMarchSpan = kMarchTiles * 64;
+// FP64: 4 wavefronts, one per SIMD, each with all 512 registers (the levels' history lies in the
+// accumulation registers), and 3 tiles.
+constexpr int kMarchWavesF64 = 4;
+constexpr int kMarchTilesF64 = 3;
+constexpr int march_waves(bool f64) { return f64 ? kMarchWavesF64 : kMarchWaves; }
+constexpr int march_tiles(bool f64) { return f64 ? kMarchTilesF64 : kMarchTiles; }
 
 struct MarchArgs {
     Common cm;
@@ -226,6 +232,7 @@ struct MarchArgs {
     float fb[kMarchMaxLevels][2];    // uniform body r(n+1+t) b0 rounded to float
     void* rec[kMarchMaxLevels];      // records of U^{n+1+t} (the replay form), or NULL
     int rec_planes;                  // 6: whole records; 4: the F - I planes 2 .. 5 only
+    int tile0, tile1, row0, row1;    // the rectangle: tiles [tile0, tile1) of the rows [row0, row1)
     int nspan, seg, nwg;             // spans per row, rows per segment, workgroups
     FastDiv d_nspan;
 };

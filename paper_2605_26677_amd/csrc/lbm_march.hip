@@ -14,14 +14,14 @@
 namespace lbm {
 
 // The LDS of one workgroup: the output row of its span, in the storage type, and the
-// accumulator words of that row; two buffers (one for FP64, whose row is twice as large)
-// so that one barrier per iteration separates the writes of a row from its reads.
+// accumulator words of that row; two buffers so that one barrier per iteration separates the
+// writes of a row from its reads.
 template <int ST, int NT, bool REC>
 struct MarchLds {
-    static constexpr int nbuf = ST == LBM_F64_PLAIN ? 1 : 2;
-    __attribute__((aligned(16))) typename Storage<ST>::pop_t pop[nbuf][24][kMarchSpan];
-    __attribute__((aligned(16))) float S[nbuf][2][kMarchSpan];
-    __attribute__((aligned(16))) double U[nbuf][2][kMarchSpan];
+    static constexpr int span = march_tiles(ST == LBM_F64_PLAIN) * kTile;
+    __attribute__((aligned(16))) typename Storage<ST>::pop_t pop[2][24][span];
+    __attribute__((aligned(16))) float S[2][2][span];
+    __attribute__((aligned(16))) double U[2][2][span];
 };
 // The replay form (REC: records of every level, no displacement accumulator): the output
 // row of the populations and the rows of the records of the NT levels.  Where two buffers
@@ -30,7 +30,6 @@ struct MarchLds {
 // iteration follows their stores.
 template <int ST, int NT>
 struct MarchLds<ST, NT, true> {
-    static constexpr int nbuf = 2;
     static constexpr int rbuf =
         2 * 24 * kMarchSpan * sizeof(typename Storage<ST>::pop_t) + 2 * NT * 6 * kMarchSpan * sizeof(float) <=
                 160 * 1024 ? 2 : 1;
@@ -43,8 +42,9 @@ template <int ST, int NT, bool REC> constexpr int rec_buffers() {
     else return 0;
 }
 
-// Geometry.  A workgroup owns a span of kMarchTiles = 7 aligned tiles (448 columns) and a
-// segment of rows; its kMarchWaves = 8 wavefronts each compute a window of 64 columns.
+// Geometry (FP32 and FP16; FP64 has 3 tiles and 4 wavefronts).  A workgroup owns a span of 7
+// aligned tiles (448 columns) and a segment of rows; its 8 wavefronts each compute a window of
+// 64 columns.
 // Level n+1 is pulled from memory on all 64 lanes; a later level pulls its x-neighbours
 // from the adjacent lanes, so each level loses one lane at either end and level n+NT is
 // complete on lanes [NT-1, 64-NT]: a window outputs OW = 64 - 2 (NT - 1) columns.  Windows
@@ -68,20 +68,25 @@ template <int ST, int NT, bool REC> constexpr int rec_buffers() {
 // lane of every wavefront (lanes, wavefronts and iterations without output store to
 // kNoStore), and before the loop one such row of empty stores follows the first loads.
 //
+// Rectangle.  The spans cover the tiles [tile0, tile1) and the segments the rows [row0, row1):
+// the whole grid when it is periodic.  On a grid with walls the rectangle keeps NT nodes away
+// from every wall line, so that no node it computes has a missing link, and patch_kernel takes
+// the rest.
+//
 // REC (the replay of the checkpointed adjoint): no displacement accumulator; the record of
 // every level (v and F - I, as lbm_step writes it) goes through LDS like the output row
 // and is stored whole per tile for the rows of the segment.
 template <int ST, int LAW, bool FIELDS, int NT, bool REC>
-__global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a) {
+__global__ void __launch_bounds__(march_waves(ST == LBM_F64_PLAIN) * kTile) march_kernel(MarchArgs a) {
     using Tr = Storage<ST>;
     using R = typename Tr::real;
     using T = typename Tr::pop_t;
     constexpr bool SH = Tr::shifted;
     constexpr int OW = kTile - 2 * (NT - 1);
-    static_assert(kMarchTiles * OW + OW >= kMarchSpan, "the windows must cover the span");
+    constexpr int tiles = march_tiles(ST == LBM_F64_PLAIN), colspan = tiles * kTile;
+    static_assert(tiles * OW + OW >= colspan, "the windows must cover the span");
     constexpr uint32_t kPlane = kTile * sizeof(T);     // bytes between planes of a tile
     static_assert(!REC || SH, "records of the shifted storages only");
-    constexpr int NB = MarchLds<ST, NT, REC>::nbuf;
     constexpr int NRB = rec_buffers<ST, NT, REC>();
     auto record_buffer = [](int i) { return NRB == 1 ? 0 : (i & 1); };
     __shared__ MarchLds<ST, NT, REC> sh;
@@ -95,19 +100,19 @@ __global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a)
     const int g = remap_tile(blockIdx.x, gridDim.x);
     if (g >= a.nwg) return;
     const int seg = fdiv(g, a.d_nspan), span = g - seg * a.nspan;
-    const int c0 = span * kMarchSpan;                   // first column of the span
-    const int ws = w < kMarchTiles ? w * OW : kMarchSpan - OW;   // window's first output column
+    const int c0 = a.tile0 * kTile + span * colspan; // first column of the span
+    const int ws = w < tiles ? w * OW : colspan - OW;   // window's first output column
     const int xg = c0 + ws - (NT - 1) + lane;
     const int xc = wrap_index(xg, nx);
     const int om = pop_col(wrap_dec(xc, nx)), oc = pop_col(xc), op = pop_col(wrap_inc(xc, nx));
     const int64_t rowe = int64_t(ntile) * 24 * kTile;  // elements per row of population tiles
     const int64_t rowu = int64_t(ntile) * 2 * kTile;   // elements per row of the u* planes
     const int ou = (xc >> 6) * (2 * kTile) + (xc & (kTile - 1));
-    const int Y0 = seg * a.seg, Sy = min(a.seg, ny - Y0);
+    const int Y0 = a.row0 + seg * a.seg, Sy = min(a.seg, a.row1 - Y0);
     // this lane's output column in the span (window 7 leaves the columns of window 6 to it)
     const int pos = ws - (NT - 1) + lane;
     const bool out_lane = lane >= NT - 1 && lane <= kTile - NT &&
-                          (w < kMarchTiles || pos >= (kMarchTiles - 1) * OW + OW);
+                          (w < tiles || pos >= (tiles - 1) * OW + OW);
     // the tile this wavefront stores (wavefront 7 stores none)
     const int st = c0 / kTile + w;
     const T* __restrict__ src = (const T*)a.src;
@@ -177,10 +182,10 @@ __global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a)
     // store sequences of different lengths here: the compiler's waits would then assume the
     // shortest, and a path that skips both would be taken as possible.
     auto store_row = [&](int yo, bool outp, int b, bool moved, int outp_iter) {
-        const bool on = outp && w < kMarchTiles && st < ntile;
+        const bool on = outp && w < tiles && st < a.tile1;
         const __amdgpu_buffer_rsrc_t rp = row_rsrc(dst + yo * rowe, rowe * int64_t(sizeof(T)));
         const uint32_t tb = uint32_t(st * 24 * kTile) * uint32_t(sizeof(T));   // tile's first byte
-        const int lc = w < kMarchTiles ? w * kTile : 0;                      // tile's LDS column
+        const int lc = w < tiles ? w * kTile : 0;                      // tile's LDS column
         constexpr int V = 16 / sizeof(T);          // elements per 16-byte piece
         constexpr int LPP = kTile / V;             // lanes per plane
         constexpr int PPI = kTile / LPP;           // planes per instruction
@@ -200,7 +205,7 @@ __global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a)
 #pragma unroll
             for (int L = 1; L <= NT; ++L) {
                 const int i0 = NT + L - 2;                  // first iteration of a segment row
-                const bool rin = outp_iter >= i0 && outp_iter < i0 + Sy && w < kMarchTiles && st < ntile;
+                const bool rin = outp_iter >= i0 && outp_iter < i0 + Sy && w < tiles && st < a.tile1;
                 const __amdgpu_buffer_rsrc_t rr = row_rsrc((float*)a.rec[L - 1] + rw[L] * rowr, rowr * 4);
                 const uint32_t tr = uint32_t(st * 6 * kTile);
                 const u32x4 v0 = *(const u32x4*)&sh.rec[rb][L - 1][pl][lc + col];
@@ -264,9 +269,8 @@ __global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a)
     // window that starts past the grid's last column but inside the last tile still runs,
     // so that the padding columns of that tile receive the wrapped copies of real nodes
     // and every stored word is defined.
-    if (c0 + ws >= ntile * kTile) {
+    if (c0 + ws >= a.tile1 * kTile) {
         for (int i = 0; i < iters; ++i) {
-            if (NB == 1) __syncthreads();
             __syncthreads();
             if constexpr (REC && NRB == 1) __syncthreads();
         }
@@ -276,7 +280,7 @@ __global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a)
     store_row(rw[NT], false, 0, false, -1);
     auto iteration = [&](int i, auto steady_c) {
         constexpr bool steady = decltype(steady_c)::value;
-        const int b = NB == 1 ? 0 : (i & 1);
+        const int b = i & 1;
         const int rb = record_buffer(i);
         // REC: the record of level t at this lane's output column into LDS buffer b
         auto stage_record = [&](int t, const R Uv[6]) {
@@ -395,7 +399,6 @@ __global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a)
                 moved = mv;
             }
         }
-        if (NB == 1) __syncthreads();               // the previous row has been read
         if (outp && out_lane) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -445,6 +448,8 @@ __global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a)
     } else {
         for (; i < iters; ++i) iteration(i, std::false_type{});
     }
+    // columns beyond the rectangle (not reached on a periodic axis) hold no node's state
+    if (a.tile1 < ntile && xg >= a.tile1 * kTile) nonfinite = jbad = false;
     if (nonfinite || jbad)
         atomicOr(cm.fault, (jbad ? (uint32_t)LBM_FAULT_J : 0u) | (nonfinite ? (uint32_t)LBM_FAULT_NONFINITE : 0u));
 }
@@ -453,7 +458,7 @@ __global__ void __launch_bounds__(kMarchWaves * kTile) march_kernel(MarchArgs a)
 
 template <int ST, int LAW, bool FIELDS>
 static hipError_t march_levels(const MarchArgs& a, hipStream_t s) {
-    const dim3 grid(unsigned(a.nwg)), block(kMarchWaves * kTile);
+    const dim3 grid(unsigned(a.nwg)), block(march_waves(ST == LBM_F64_PLAIN) * kTile);
     if (a.rec[0]) {
         // the replay form: records of every level, no accumulator
         if constexpr (ST != LBM_F64_PLAIN) {

@@ -120,3 +120,23 @@ def test_steps_from_a_lent_buffer_leave_it_unchanged():
     torch.cuda.synchronize()
     assert torch.equal(snap, keep)
     assert torch.equal(a.populations(), b.populations())
+
+
+@pytest.mark.parametrize("walls", ["all_traction", "mixed", "x_periodic", "y_periodic"])
+@pytest.mark.parametrize("nx,ny", [(1151, 1103), (256, 4900), (4899, 260)])
+def test_large_walled_grids(nx, ny, walls):
+    """The inner rectangle in multi-level launches and the patches around it: widths that leave
+    4 and more columns beyond the last whole tile, every remainder of the levels."""
+    compare(nx, ny, "f32", "lognh", walls, True, 9, n0=11)
+    compare(nx, ny, "f16", "svk", walls, False, 6)
+
+
+@pytest.mark.parametrize("nx", [1152, 1154, 1155, 1156, 1157])
+def test_large_walled_grid_widths(nx):
+    compare(nx, 1103, "f32", "nh", "mixed", False, 5, n0=13)
+
+
+@pytest.mark.parametrize("planes", [4, 6])
+def test_large_walled_grid_records(planes):
+    compare(1151, 1103, "f32", "lognh", "mixed", True, 10, records=planes)
+    compare(1151, 1103, "f16", "gent", "x_periodic", True, 5, records=planes)
