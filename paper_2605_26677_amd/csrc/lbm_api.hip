@@ -492,12 +492,13 @@ bool invariant_material(const lbm_params* p) {
 // round the larger of `level` (one node's chain of dependent instructions and the barrier, with
 // walls the traction solves before it) and `wave` for every wavefront of the level, of which
 // patches of one compute unit beyond the first add the share `share` (they fill each other's
-// waits).  `waves` wavefronts fit a compute unit.  Fitted to sweeps over 2 .. 8 levels and
-// patches of 4 x 4 to 32 x 16 nodes on 18 grids of 64 x 64 to 1024 x 1024 nodes (log-NH and Gent):
-// the chosen plan is 4 % slower than the best of the sweep on average (FP64 with walls 11 %).  Patches are
-// used up to `side`^2 nodes.
+// waits).  Patches of 32 columns cost `row` times that (FP32 rows of 32 nodes are whole cache
+// lines: 256^2, 6 levels 2.39 us per level at 32 x 8, 2.66 at 16 x 16).  `waves` wavefronts fit
+// a compute unit.  Fitted to sweeps over 2 .. 8 levels and patches of 4 x 4 to 32 x 16 nodes on
+// 18 grids of 64 x 64 to 1024 x 1024 nodes (log-NH and Gent): the chosen plan is 1 to 5 % slower
+// than the best of the sweep on average, 25 % at worst.  Patches are used up to `side`^2 nodes.
 struct PatchCost {
-    double launch, level, wave, round, share;
+    double launch, level, wave, round, share, row;
     int side, threads, waves;
 };
 
@@ -524,9 +525,7 @@ PatchPlan patch_choice(const lbm_params* p, const PatchCost& c, int words, bool 
             for (int k = 0; k < T; ++k)
                 t += std::max(c.level * rounds, c.wave * ((per_cu - 1) * c.share + 1.0) *
                                                     (((pw + 2 * k) * (ph + 2 * k) + kTile - 1) / kTile));
-            // rows of 32 nodes read and write whole cache lines (256^2 FP32, 6 levels: 2.39 us
-            // per level at 32 x 8, 2.66 at 16 x 16)
-            if (pw >= 32) t *= 0.92;
+            if (pw >= 32) t *= c.row;
             if (best.levels == 0 || t / T < least) {
                 least = t / T;
                 best = PatchPlan{T, pw, ph};
@@ -550,23 +549,27 @@ PatchPlan patch_choice(const lbm_params* p, const PatchCost& c, int words, bool 
 // (the traction solves of a wall node, some 700 dependent instructions per level, bound the
 // small walled grids).
 PatchPlan patch_plan(const lbm_params* p) {
-    static const PatchCost kShifted{12.7, 0.84, 0.457, 3.43, 1.0, 1150, patch_threads(false, false), 24};
-    static const PatchCost kShiftedWalls{18.4, 1.37, 0.090, 3.58, 0.57, 1100, patch_threads(false, true), 24};
-    static const PatchCost kPlain{7.71, 8.22, 1.31, 3.42, 0.96, 750, patch_threads(true, false), 12};
-    static const PatchCost kPlainWalls{7.40, 2.22, 0.341, 3.28, 0.79, 700, patch_threads(true, true), 12};
-    const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN, half = p->storage == LBM_F16_SHIFTED;
+    static const PatchCost kShifted{12.7, 0.84, 0.457, 3.43, 1.0, 0.92, 1150, patch_threads(false, false), 24};
+    static const PatchCost kVelocity{2.80, 0.306, 0.032, 0.600, 1.0, 0.92, 1100, patch_threads(false, false), 24};
+    static const PatchCost kTraction{18.4, 1.37, 0.090, 3.58, 0.57, 1.0, 1100, patch_threads(false, true), 24};
+    static const PatchCost kHalf{12.7, 0.84, 0.457, 3.43, 1.0, 1.0, 1150, patch_threads(false, false), 24};
+    static const PatchCost kHalfVelocity{12.7, 0.84, 0.457, 3.43, 1.0, 1.0, 1100, patch_threads(false, false), 24};
+    static const PatchCost kPlain{7.71, 8.22, 1.31, 3.42, 0.96, 1.0, 750, patch_threads(true, false), 12};
+    static const PatchCost kPlainTraction{22.0, 2.19, 0.872, 0.921, 0.129, 1.0, 750, patch_threads(true, true), 12};
+    const bool walls = any_wall(p), traction = has_traction(p);
+    const bool plain = p->storage == LBM_F64_PLAIN, half = p->storage == LBM_F16_SHIFTED;
     const int64_t nodes = int64_t(p->nx) * p->ny;
     // FP16 pairs move half the bytes: they win where their grids fit the caches (638 x 339: 4.3
-    // us per level, patches 5.4; 404^2 and 584^2 are 3 and 17 % slower in pairs), and on large
-    // grids without traction edges (756 x 1095 4 %)
+    // us per level, patches 5.4; 404^2 and 584^2 are 3 and 17 % slower in pairs)
     if (half && !walls && nodes > 430 * 430 && nodes < 530 * 530) return PatchPlan{0, 0, 0};
-    if (half && walls && !has_traction(p) && nodes > 860 * 860) return PatchPlan{0, 0, 0};
     // large grids: many rounds of small workgroups, three to a compute unit (1000 x 777: 11.8 us
     // per level, 13.9 with the least-cost plan)
     if (!plain && !walls && nodes > 720 * 720 && nodes <= int64_t(kShifted.side) * kShifted.side && p->nx >= 32)
         return PatchPlan{3, 32, std::min(8, p->ny)};
-    return patch_choice(p, plain ? (walls ? kPlainWalls : kPlain) : (walls ? kShiftedWalls : kShifted),
-                        walls ? 27 : 25, false);
+    const PatchCost& c = plain ? (traction ? kPlainTraction : kPlain)
+                               : traction ? kTraction
+                                          : half ? (walls ? kHalfVelocity : kHalf) : (walls ? kVelocity : kShifted);
+    return patch_choice(p, c, traction ? 27 : 25, false);
 }
 
 enum Route { kRouteStep, kRoutePair, kRouteMulti, kRouteRim, kRoutePatch };
@@ -639,8 +642,11 @@ Inner inner_rect(const lbm_params* p, int levels, int ph) {
     return in;
 }
 
-// The patches of the whole grid, those along walls first (their traction solves take longer),
-// or of the grid outside the rectangle `in`.
+// The patches of the whole grid, those whose region reaches a wall first (their traction solves
+// take longer, and the first workgroups are dealt over the XCDs one by one; with only the ragged
+// last row and column among the first, the far walls of a grid of whole patches came last and on
+// one XCD: 384^2 FP64 Gent 23.3 -> 14.3 us per level, 512^2 FP32 log-NH 10.4 -> 8.5), or of the
+// grid outside the rectangle `in`.
 PatchMap patch_map(const lbm_params* p, const PatchPlan& pl, const Inner* in = nullptr) {
     PatchMap m{};
     m.pw = pl.pw;
@@ -659,9 +665,12 @@ PatchMap patch_map(const lbm_params* p, const PatchPlan& pl, const Inner* in = n
     };
     const bool perx = p->bc[LBM_XMIN] == LBM_PERIODIC, pery = p->bc[LBM_YMIN] == LBM_PERIODIC;
     const int pw = pl.pw, ph = pl.ph;
-    int x1 = perx ? 0 : std::min(pw, p->nx), y1 = pery ? 0 : std::min(ph, p->ny);
-    int x2 = perx ? p->nx : std::max(x1, p->nx / pw * pw);
-    int y2 = pery ? p->ny : std::max(y1, p->ny / ph * ph);
+    const int halo = pl.levels - 1;
+    auto low = [halo](int w, int n) { return std::min((halo / w + 1) * w, n); };
+    auto high = [halo](int w, int n, int lo) { return std::max(lo, (std::max(n - halo - w, 0) + w - 1) / w * w); };
+    int x1 = perx ? 0 : low(pw, p->nx), y1 = pery ? 0 : low(ph, p->ny);
+    int x2 = perx ? p->nx : std::min(high(pw, p->nx, x1), p->nx);
+    int y2 = pery ? p->ny : std::min(high(ph, p->ny, y1), p->ny);
     if (in) {
         x1 = in->tile0 * kTile;
         x2 = std::min(in->tile1 * kTile, p->nx);
@@ -720,14 +729,14 @@ lbm_status patch_launch(const lbm_params* p, lbm_state* s, int64_t n, const Patc
 // 1024^2 47 / 43; walls 512^2 16.4 / 35.7, 1024^2 57 / 65; FP64 256^2 8.2 / 8.4, 512^2 29 / 30,
 // walls 512^2 39 / 53, 1024^2 154 / 134).
 PatchPlan patch_adj_plan(const lbm_params* p) {
-    static const PatchCost kShifted{24.6, 2.20, 0.585, 67.3, 0.83, 900, kPatchAdjThreads, 24};
-    static const PatchCost kShiftedWalls{2.92, 0.78, 0.081, 11.0, 0.86, 1300, kPatchAdjThreads, 24};
-    static const PatchCost kPlain{13.6, 0.96, 0.121, 1.46, 0.70, 800, kPatchAdjThreads, 12};
-    static const PatchCost kPlainWalls{2.01, 5.73, 0.732, 1.65, 1.0, 780, kPatchAdjThreads, 12};
-    static const PatchCost kInvShifted{3.18, 4.20, 0.808, 0.66, 0.54, 920, kPatchAdjThreads, 24};
-    static const PatchCost kInvShiftedWalls{3.09, 37.5, 4.19, 6.26, 0.55, 1030, kPatchAdjThreads, 24};
-    static const PatchCost kInvPlain{10.8, 20.7, 2.81, 1.91, 0.90, 420, kPatchAdjThreads, 12};
-    static const PatchCost kInvPlainWalls{3.77, 13.0, 1.50, 2.38, 1.0, 700, kPatchAdjThreads, 12};
+    static const PatchCost kShifted{24.6, 2.20, 0.585, 67.3, 0.83, 1.0, 900, kPatchAdjThreads, 24};
+    static const PatchCost kShiftedWalls{25.9, 1.19, 0.123, 15.5, 0.436, 1.0, 1300, kPatchAdjThreads, 24};
+    static const PatchCost kPlain{6.58, 0.230, 0.0297, 2.43, 0.626, 1.0, 800, kPatchAdjThreads, 12};
+    static const PatchCost kPlainWalls{2.01, 5.73, 0.732, 1.65, 1.0, 1.0, 780, kPatchAdjThreads, 12};
+    static const PatchCost kInvShifted{3.18, 4.20, 0.808, 0.66, 0.54, 1.0, 920, kPatchAdjThreads, 24};
+    static const PatchCost kInvShiftedWalls{3.09, 37.5, 4.19, 6.26, 0.55, 1.0, 1030, kPatchAdjThreads, 24};
+    static const PatchCost kInvPlain{10.8, 20.7, 2.81, 1.91, 0.90, 1.0, 420, kPatchAdjThreads, 12};
+    static const PatchCost kInvPlainWalls{3.77, 13.0, 1.50, 2.38, 1.0, 1.0, 700, kPatchAdjThreads, 12};
     const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN;
     const PatchCost& c = invariant_material(p)
                              ? (plain ? (walls ? kInvPlainWalls : kInvPlain) : (walls ? kInvShiftedWalls : kInvShifted))

@@ -263,7 +263,7 @@ struct MarchAdjArgs {
 constexpr int kPatchLevels = 8;          // most levels per launch
 // most nodes of a patch with its halo: FP64 and the traction solves take more registers than a
 // workgroup of 1024 threads leaves to each
-constexpr int patch_threads(bool plain, bool walls) { return plain || walls ? 512 : 1024; }
+constexpr int patch_threads(bool plain, bool traction) { return plain || traction ? 512 : 1024; }
 constexpr int kPatchAdjThreads = 512;    // the same for the adjoint
 constexpr int kPatchLds = 160 * 1024;    // LDS of a compute unit
 constexpr int kPatchRects = 5;

@@ -21,26 +21,46 @@
 
 namespace lbm {
 
-// The missing link of a wall node whose edge's normal lies along axis AX (lo: the edge at
-// coordinate 0, else the one at the far end), at position s of the edge, from the node's own
-// outgoing populations o, its F of the same level (U[2 .. 5]; traction edges) and the boundary
-// data of the step.  Returns false when the traction solve failed.
+// The boundary data of step t of the launch at position s of the edge whose normal lies along
+// axis AX (lo: the edge at coordinate 0, else the one at the far end).
+template <typename R, int AX>
+__device__ __forceinline__ void patch_edge_data(const PatchArgs& a, int t, bool lo, int s, R w[2]) {
+    constexpr int E0 = AX == 0 ? LBM_XMIN : LBM_YMIN, E1 = E0 + 1;
+    const int L = AX == 0 ? a.cm.ny : a.cm.nx;
+    const double* fl = lo ? a.field[t][E0] : a.field[t][E1];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) w[c] = fl ? R(fl[c * L + s]) : lo ? R(a.value[t][E0][c]) : R(a.value[t][E1][c]);
+}
+
+// The missing link of a wall node from its own outgoing populations o and its F of the same
+// level (U[2 .. 5]; traction edges).  Returns false when the traction solve failed.
 template <typename R, int LAW, bool SH, int AX>
 __device__ __forceinline__ bool patch_link(const PatchArgs& a, int t, bool lo, int s, const R o[6], const R U[6],
                                            R mu, R lam, R out[6]) {
     const Common& cm = a.cm;
-    constexpr int E0 = AX == 0 ? LBM_XMIN : LBM_YMIN, E1 = E0 + 1;
-    const int L = AX == 0 ? cm.ny : cm.nx;
-    const double* fl = lo ? a.field[t][E0] : a.field[t][E1];
-    R w[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) w[c] = fl ? R(fl[c * L + s]) : lo ? R(a.value[t][E0][c]) : R(a.value[t][E1][c]);
-    const bool velocity = (lo ? cm.bc[E0] : cm.bc[E1]) == LBM_VELOCITY;
     const R NA = lo ? R(-1) : R(1);
-    R Fb[4] = {R(0), R(0), R(0), R(0)};
+    const bool velocity = (AX == 0 ? (lo ? cm.bc[LBM_XMIN] : cm.bc[LBM_XMAX])
+                                   : (lo ? cm.bc[LBM_YMIN] : cm.bc[LBM_YMAX])) == LBM_VELOCITY;
+    R w[2], Fb[4] = {R(0), R(0), R(0), R(0)};
+    patch_edge_data<R, AX>(a, t, lo, s, w);
     const bool ok = velocity || boundary_F<R, LAW, SH, AX>(cm, NA, U, w, mu, lam, Fb);
     wall_rule<R>(velocity, AX == 0 ? NA : R(0), AX == 1 ? NA : R(0), w[0], w[1], R(cm.c), o, Fb, out);
     return ok;
+}
+
+// The missing link of a velocity wall node, into the slot it is read from.  o: the node's
+// outgoing populations, `stride` apart.
+template <typename R, int AX, typename T>
+__device__ __forceinline__ void patch_velocity_link(const PatchArgs& a, int t, bool lo, int s, const T* o, int stride,
+                                                    R* slot) {
+    const R NA = lo ? R(-1) : R(1), none[4] = {R(0), R(0), R(0), R(0)};
+    R w[2], in[6], out[6];
+    patch_edge_data<R, AX>(a, t, lo, s, w);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) in[k] = R(o[k * stride]);
+    wall_rule<R>(true, AX == 0 ? NA : R(0), AX == 1 ? NA : R(0), w[0], w[1], R(a.cm.c), in, none, out);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) slot[k] = out[k];
 }
 
 // Exchange through LDS.  A node's 24 populations, rounded to the storage type, take 25
@@ -50,16 +70,20 @@ __device__ __forceinline__ bool patch_link(const PatchArgs& a, int t, bool lo, i
 // the neighbour it streams to; the next level then reads f_q from slot opp(q) of the
 // neighbour it pulls from (t even) or from its own slot q (t odd).  A node writes exactly the
 // slots it has just read, so one barrier per level separates the levels.
-// (27 with per-node parameters on a grid with walls: mu and lam for the link solves)
+// (27 with per-node parameters on a grid with traction edges: mu and lam for the link solves)
 constexpr int patch_stride(bool params) { return params ? 27 : 25; }
 
-template <int ST, int LAW, bool WALLS, bool FIELDS>
-__global__ void __launch_bounds__(patch_threads(ST == LBM_F64_PLAIN, WALLS)) patch_kernel(PatchArgs a) {
+// Grids without walls, with velocity walls only, and with traction edges.
+enum { kNoWalls, kVelocityWalls, kTractionWalls };
+
+template <int ST, int LAW, int WALLS, bool FIELDS>
+__global__ void __launch_bounds__(patch_threads(ST == LBM_F64_PLAIN, WALLS == kTractionWalls)) patch_kernel(PatchArgs a) {
     using Tr = Storage<ST>;
     using R = typename Tr::real;
     using T = typename Tr::pop_t;
     constexpr bool SH = Tr::shifted;
-    constexpr int NS = patch_stride(WALLS && FIELDS);
+    constexpr bool LINKS = WALLS == kTractionWalls;
+    constexpr int NS = patch_stride(LINKS && FIELDS);
     extern __shared__ __attribute__((aligned(16))) char patch_smem[];
     R* sh = (R*)patch_smem;
     const Common& cm = a.cm;
@@ -96,7 +120,7 @@ __global__ void __launch_bounds__(patch_threads(ST == LBM_F64_PLAIN, WALLS)) pat
             bf[0] = cm.body[idx];
             bf[1] = cm.body[n + idx];
         }
-        if (WALLS && FIELDS) {
+        if (LINKS && FIELDS) {
             own[NS - 2] = mu;
             own[NS - 1] = lam;
         }
@@ -126,14 +150,14 @@ __global__ void __launch_bounds__(patch_threads(ST == LBM_F64_PLAIN, WALLS)) pat
         }
     };
     uint32_t fault = 0;
-    // A patch whose region touches a wall solves the missing links of a level first: one lane
+    // Grids with traction edges: a patch whose region touches a wall solves the missing links of a level first: one lane
     // per link, the links of x-edges and of y-edges on wavefronts of their own, so that no
     // wavefront takes one solve after the other.  A link reads its node's populations of level
     // n + t - 1 (in memory, or where the node wrote them in LDS) and writes its value into the
     // slot the node is about to read (a slot whose neighbour lies beyond the wall: no other
     // thread touches it).
     const int halo = levels - 1;
-    const bool rim = WALLS && ((!cm.periodic_x && (px0 - halo <= 0 || px0 + pw + halo >= nx)) ||
+    const bool rim = LINKS && ((!cm.periodic_x && (px0 - halo <= 0 || px0 + pw + halo >= nx)) ||
                                (!cm.periodic_y && (py0 - halo <= 0 || py0 + ph + halo >= ny)));
     auto solve_links = [&](int t, int px0, int py0) {
         asm volatile("" : "+s"(px0), "+s"(py0));     // formed here, not kept through the loop
@@ -198,6 +222,30 @@ __global__ void __launch_bounds__(patch_threads(ST == LBM_F64_PLAIN, WALLS)) pat
         int x = xr, y = yr;
         asm volatile("" : "+v"(x), "+v"(y));
         R gq[4][6], f[4][6];
+        // Velocity walls alone: a link takes no solve, and the node's own thread forms it from the
+        // populations that it wrote itself, so that the patches at a wall have one barrier per
+        // level as all others (128^2 FP32 @@ -> @@ us per level, 512^2 FP64 @@ -> @@, against the
+        // lanes and barriers of solve_links; where only some of the edges are velocity walls
+        // the solves' lanes take these links along).
+        if (WALLS == kVelocityWalls && act && (xw || yw)) {
+            const bool nbr = (t & 1) == 0;
+            const T* s = src + tile_base(ntile, 24, x, y);
+            if (xw) {
+                const bool lo = x == 0;
+                // the outgoing q2 at XMIN (q0 at XMAX) lies where level t - 1 wrote it
+                R* slot = lo ? (nbr ? nb0 + 12 : own) : (nbr ? nb2 : own + 12);
+                const R* o = lo ? (nbr ? own : nb0 + 12) : (nbr ? own + 12 : nb2);
+                if (t == 1) patch_velocity_link<R, 0>(a, t - 1, lo, y, s + (lo ? 12 : 0) * kTile, kTile, slot);
+                else patch_velocity_link<R, 0>(a, t - 1, lo, y, o, 1, slot);
+            }
+            if (yw) {
+                const bool lo = y == 0;
+                R* slot = lo ? (nbr ? nb1 + 18 : own + 6) : (nbr ? nb3 + 6 : own + 18);
+                const R* o = lo ? (nbr ? own + 6 : nb1 + 18) : (nbr ? own + 18 : nb3 + 6);
+                if (t == 1) patch_velocity_link<R, 1>(a, t - 1, lo, x, s + (lo ? 18 : 6) * kTile, kTile, slot);
+                else patch_velocity_link<R, 1>(a, t - 1, lo, x, o, 1, slot);
+            }
+        }
         if (rim) {
             if (FIELDS || t > 1) __syncthreads();
             solve_links(t, px0, py0);
@@ -328,22 +376,27 @@ __global__ void __launch_bounds__(patch_threads(ST == LBM_F64_PLAIN, WALLS)) pat
 
 // ---------------------------------------------------------------- dispatch
 
+template <int ST, int LAW, int WALLS>
+static hipError_t patch_st_law_walls(const PatchArgs& a, hipStream_t s) {
+    const bool fields = a.cm.mu || a.cm.lam || a.cm.body;
+    const int nodes = (a.map.pw + 2 * (a.levels - 1)) * (a.map.ph + 2 * (a.levels - 1));
+    const size_t lds =
+        size_t(nodes) * patch_stride(WALLS == kTractionWalls && fields) * sizeof(typename Storage<ST>::real);
+    const dim3 grid(unsigned(a.map.nwg)), block(unsigned((nodes + kTile - 1) / kTile * kTile));
+    if (block.x > unsigned(patch_threads(ST == LBM_F64_PLAIN, WALLS == kTractionWalls)) || lds > size_t(kPatchLds))
+        return hipErrorInvalidValue;
+    if (fields) hipLaunchKernelGGL((patch_kernel<ST, LAW, WALLS, true>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((patch_kernel<ST, LAW, WALLS, false>), grid, block, lds, s, a);
+    return hipGetLastError();
+}
+
 template <int ST, int LAW>
 static hipError_t patch_st_law(const PatchArgs& a, hipStream_t s) {
-    const bool fields = a.cm.mu || a.cm.lam || a.cm.body;
-    const bool walls = !(a.cm.periodic_x && a.cm.periodic_y);
-    const int nodes = (a.map.pw + 2 * (a.levels - 1)) * (a.map.ph + 2 * (a.levels - 1));
-    const size_t lds = size_t(nodes) * patch_stride(walls && fields) * sizeof(typename Storage<ST>::real);
-    const dim3 grid(unsigned(a.map.nwg)), block(unsigned((nodes + kTile - 1) / kTile * kTile));
-    if (block.x > unsigned(patch_threads(ST == LBM_F64_PLAIN, walls)) || lds > size_t(kPatchLds)) return hipErrorInvalidValue;
-    if (walls) {
-        if (fields) hipLaunchKernelGGL((patch_kernel<ST, LAW, true, true>), grid, block, lds, s, a);
-        else hipLaunchKernelGGL((patch_kernel<ST, LAW, true, false>), grid, block, lds, s, a);
-    } else {
-        if (fields) hipLaunchKernelGGL((patch_kernel<ST, LAW, false, true>), grid, block, lds, s, a);
-        else hipLaunchKernelGGL((patch_kernel<ST, LAW, false, false>), grid, block, lds, s, a);
-    }
-    return hipGetLastError();
+    if (a.cm.periodic_x && a.cm.periodic_y) return patch_st_law_walls<ST, LAW, kNoWalls>(a, s);
+    bool traction = false;
+    for (int e = 0; e < 4; ++e) traction |= a.cm.bc[e] == LBM_TRACTION;
+    if (traction) return patch_st_law_walls<ST, LAW, kTractionWalls>(a, s);
+    return patch_st_law_walls<ST, LAW, kVelocityWalls>(a, s);
 }
 
 template <int ST>

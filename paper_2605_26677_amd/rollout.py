@@ -24,7 +24,7 @@ from typing import Callable, Optional, Sequence
 import torch
 
 from . import _lib as L
-from .solver import EdgeData, Solver, _ptr, _stream, fill_edges, host_matrix
+from .solver import EdgeData, Solver, _ptr, _stream, host_matrix, pack_edges
 
 
 @dataclass
@@ -379,12 +379,7 @@ class _Adjoint:
         recs = (ctypes.c_void_p * k)(*[rec.data_ptr() for rec in records])
         ed, held = None, []
         if not sv.periodic:
-            ed = (L.lbm_edge_data * k)()
-            if cfg.edges is not None:
-                for t in range(k):
-                    v = cfg.edges(m - t)
-                    if v is not None:
-                        fill_edges(ed[t], v, held)
+            ed = pack_edges([None if cfg.edges is None else cfg.edges(m - t) for t in range(k)], held)
         L.check(sv.lib.lbm_adjoint_advance(ctypes.byref(sv.p), ctypes.byref(sv.s), ctypes.byref(self.a), int(m), int(k),
                                            r, ed, recs, _stream()), "lbm_adjoint_advance")
 

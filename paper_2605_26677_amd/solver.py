@@ -37,6 +37,42 @@ def fill_edges(c, values, keep):
             pair[1] = float(v[1])
 
 
+def pack_edges(edges, keep):
+    """The boundary data of consecutive half steps (four entries each, as fill_edges takes them,
+    EdgeData or None) as a C array of lbm_edge_data: values are gathered in one Python list and
+    converted at once (1 us per half step; element by element through ctypes it took 4, more than
+    a level of a small walled grid takes on the device)."""
+    n = len(edges)
+    out = (L.lbm_edge_data * n)()
+    flat, special = [], []
+    add = flat.append
+    for i, ed in enumerate(edges):
+        if ed is None or isinstance(ed, EdgeData):
+            if ed is not None:
+                special.append((i, ed))
+            flat.extend((0.0,) * 8)
+            continue
+        for e in range(4):
+            v = ed[e]
+            if v is None:
+                add(0.0)
+                add(0.0)
+            elif isinstance(v, torch.Tensor):
+                add(0.0)
+                add(0.0)
+                t = v.to(torch.float64).contiguous()
+                keep.append(t)
+                out[i].field[e] = t.data_ptr()
+            else:
+                add(float(v[0]))
+                add(float(v[1]))
+    words = np.frombuffer(out, dtype=np.float64).reshape(n, ctypes.sizeof(L.lbm_edge_data) // 8)
+    words[:, :8] = np.array(flat, dtype=np.float64).reshape(n, 8)
+    for i, ed in special:
+        out[i] = ed.c
+    return out
+
+
 class EdgeData:
     """Boundary data at one half step: per edge either a pair (uniform along the edge) or
     a (2, L) float64 device tensor."""
@@ -369,14 +405,8 @@ class Solver:
         if count < 1:
             return
         ra = (ctypes.c_double * (count + 1))(*r)
-        ea, held = None, []
-        if edges is not None:
-            ea = (L.lbm_edge_data * count)()
-            for i, e in enumerate(edges):
-                if isinstance(e, EdgeData):
-                    ea[i] = e.c
-                elif e is not None:
-                    fill_edges(ea[i], e, held)
+        held = []
+        ea = None if edges is None else pack_edges(edges, held)
         rec = None
         if records is not None:
             rec = (ctypes.c_void_p * count)(*[None if t is None else t.data_ptr() for t in records])
