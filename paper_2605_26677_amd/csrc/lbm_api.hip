@@ -538,18 +538,21 @@ PatchPlan patch_choice(const lbm_params* p, const PatchCost& c, int words, bool 
 // The plan of patch_kernel.  Where it stops (side) the other kernels are faster.  Measured us
 // per level, patches against the pairs, single steps and multi-level launches they replace
 // (log-NH, uniform parameters):
-//   FP32 periodic  64^2 1.7 / 2.8, 256^2 2.4 / 2.9, 512^2 5.2 / 8.3, 1024^2 14.6 / 17.4, and
-//                  1448^2 42 / 28 (march_kernel from 1150^2 on)
-//   FP32 walls     64^2 5.1 / 10.8, 256^2 6.3 / 10.6, 512^2 8.5 / 18.4, 1024^2 22.5 / 32.9
+//   FP32 periodic  64^2 1.7 / 2.8, 256^2 2.2 / 2.9, 512^2 5.2 / 8.3, 1000^2 15.2 / 23.1, and
+//                  1130^2 27.7 / 19.6 (march_kernel from 1024^2 on; FP16 16.7 / 19.0, svk with
+//                  per-node mu and lam 18.2 / 19.1)
+//   FP32 traction  64^2 5.6 / 11.7, 256^2 6.2 / 11.6, 512^2 8.5 / 18.7, 1024^2 20.9 / 33.8
 //                  (from 1100^2 on the march of the inner rectangle, see kRimNodes)
+//   FP32 velocity  64^2 2.7 / 5.3, 256^2 3.6 / 6.0, 512^2 6.5 / 12.1, 1024^2 16.1 / 25.7; FP16
+//                  512^2 7.0 / 9.5, 1024^2 17.0 / 21.7
 //   FP64 periodic  64^2 2.0 / 3.8, 256^2 3.5 / 4.1, 700^2 15.4 / 22.8, 1024^2 48 / 43; with
 //                  records 600^2 13.8 / 18.5, 850^2 41 / 38
-//   FP64 walls     64^2 9.4 / 13.9, 256^2 9.6 / 15.4, 700^2 22.6 / 39.8, 1024^2 62 / 60; between
-//                  two velocity walls with records 512^2 17 / 23, 850^2 56 / 46
+//   FP64 traction  64^2 8.9 / 15.1, 256^2 9.1 / 16.3, 640^2 19.7 / 36.9, 850^2 39.8 / 38.1
+//   FP64 velocity  64^2 3.2 / 5.6, 256^2 4.8 / 7.2, 640^2 14.3 / 27.2, 850^2 33.6 / 29.6
 // (the traction solves of a wall node, some 700 dependent instructions per level, bound the
 // small walled grids).
 PatchPlan patch_plan(const lbm_params* p) {
-    static const PatchCost kShifted{12.7, 0.84, 0.457, 3.43, 1.0, 0.92, 1150, patch_threads(false, false), 24};
+    static const PatchCost kShifted{12.7, 0.84, 0.457, 3.43, 1.0, 0.92, 1024, patch_threads(false, false), 24};
     static const PatchCost kVelocity{2.80, 0.306, 0.032, 0.600, 1.0, 0.92, 1100, patch_threads(false, false), 24};
     static const PatchCost kTraction{18.4, 1.37, 0.090, 3.58, 0.57, 1.0, 1100, patch_threads(false, true), 24};
     static const PatchCost kHalf{12.7, 0.84, 0.457, 3.43, 1.0, 1.0, 1150, patch_threads(false, false), 24};
@@ -562,13 +565,13 @@ PatchPlan patch_plan(const lbm_params* p) {
     // FP16 pairs move half the bytes: they win where their grids fit the caches (638 x 339: 4.3
     // us per level, patches 5.4; 404^2 and 584^2 are 3 and 17 % slower in pairs)
     if (half && !walls && nodes > 430 * 430 && nodes < 530 * 530) return PatchPlan{0, 0, 0};
-    // large grids: many rounds of small workgroups, three to a compute unit (1000 x 777: 11.8 us
-    // per level, 13.9 with the least-cost plan)
-    if (!plain && !walls && nodes > 720 * 720 && nodes <= int64_t(kShifted.side) * kShifted.side && p->nx >= 32)
-        return PatchPlan{3, 32, std::min(8, p->ny)};
     const PatchCost& c = plain ? (traction ? kPlainTraction : kPlain)
                                : traction ? kTraction
                                           : half ? (walls ? kHalfVelocity : kHalf) : (walls ? kVelocity : kShifted);
+    // large grids: many rounds of small workgroups, three to a compute unit (1000 x 777: 11.8 us
+    // per level, 13.9 with the least-cost plan)
+    if (!plain && !walls && nodes > 720 * 720 && nodes <= int64_t(c.side) * c.side && p->nx >= 32)
+        return PatchPlan{3, 32, std::min(8, p->ny)};
     return patch_choice(p, c, traction ? 27 : 25, false);
 }
 

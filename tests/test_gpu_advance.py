@@ -140,3 +140,28 @@ def test_large_walled_grid_widths(nx):
 def test_large_walled_grid_records(planes):
     compare(1151, 1103, "f32", "lognh", "mixed", True, 10, records=planes)
     compare(1151, 1103, "f16", "gent", "x_periodic", True, 5, records=planes)
+
+
+# walls that are all velocity walls take a kernel of their own
+VELOCITY = {
+    "x_channel": ("periodic", "periodic", "velocity", "velocity"),
+    "y_channel": ("velocity", "velocity", "periodic", "periodic"),
+    "all_velocity": ("velocity",) * 4,
+}
+LAYOUTS.update(VELOCITY)
+
+
+@pytest.mark.parametrize("walls", list(VELOCITY))
+@pytest.mark.parametrize("storage", ["f32", "f64", "f16"])
+@pytest.mark.parametrize("nx,ny", [(4, 4), (5, 7), (64, 64), (130, 61), (385, 384)])
+def test_steps_between_velocity_walls(nx, ny, storage, walls):
+    """The smallest grids, whole patches, remainders, and grids of more patches than compute
+    units: levels that end on odd and even steps, corners of two velocity walls, records."""
+    compare(nx, ny, storage, "lognh", walls, False, 21)
+    compare(nx, ny, storage, "gent", walls, True, 5, n0=30)
+    compare(nx, ny, storage, "nh", walls, True, 8, records=4)
+
+
+@pytest.mark.parametrize("walls", list(VELOCITY))
+def test_large_grids_between_velocity_walls(walls):
+    compare(1151, 1103, "f32", "lognh", walls, True, 9, n0=11)
