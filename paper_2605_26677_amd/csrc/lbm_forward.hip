@@ -292,12 +292,21 @@ __device__ __forceinline__ R acoustic_max(const R C[16], R n0, R n1) {
     return tr + sqrt_r(dd * dd + off * off);
 }
 
-// Bounds of a node's scan, in FP32.  With phi = 2 theta the entries of Q are first-order
-// trigonometric polynomials, the larger eigenvalue is T(phi) + sqrt(S(phi)), T of first and S
-// of second order, so 16 samples bound it over all directions: between two samples T and S
-// exceed their chords by at most |T''| h^2/8 and |S''| h^2/8 (h = pi/8), and the square root
-// of a linear S its own chord by (dS)^2 / (32 Smin^(3/2)).  lo is the largest sample, hi the
-// bound (not finite where S may vanish or the state is not finite: no bound).
+// Bounds of a node's scan, in FP32: lo <= the largest of its kScanDirs values <= hi.  With
+// phi = 2 theta the entries of Q are first-order trigonometric polynomials, the larger eigenvalue
+// is T(phi) + sqrt(S(phi)), T of first and S of second order.  The samples are kBoundDirs of the
+// scan's own directions, so that the largest one is no larger than the scan (between them a
+// compressed St. Venant-Kirchhoff node exceeded its own scan by up to 38 %, and a node with a
+// larger scan was skipped).  They bound the eigenvalue from above too: between two samples T and S
+// exceed their chords by at most |T''| h^2/8 and |S''| h^2/8 (h the step of phi), and the square
+// root of a linear S its own chord by (dS)^2 / (32 Smin^(3/2)).  Both bounds keep 4e-5 of the
+// largest |C_iAkB| apart from the samples: the FP32 scan's rotated directions drift by 5e-6 in
+// |n|^2 and 6e-7 in angle, and |Q| <= |C| (Frobenius, at most 4 times that entry); with the
+// rounding of either side that makes 8e-6 |C|.  hi is not finite where S may vanish or the state is not
+// finite: no bound.
+constexpr int kBoundDirs = 15;                       // every twelfth direction of the scan (18: 3 % slower)
+static_assert(kScanDirs % kBoundDirs == 0, "the samples are directions of the scan");
+
 template <typename R>
 __device__ __forceinline__ void scan_bounds(const R C[16], float& lo, float& hi) {
     float z[3][3];                                  // T, (Q00 - Q11)/2, (Q01 + Q10)/2
@@ -314,6 +323,9 @@ __device__ __forceinline__ void scan_bounds(const R C[16], float& lo, float& hi)
             z[m][j] = m == 0 ? 0.5f * (coef(0, 0, j) + coef(1, 1, j))
                     : m == 1 ? 0.5f * (coef(0, 0, j) - coef(1, 1, j)) : 0.5f * (coef(0, 1, j) + coef(1, 0, j));
     }
+    float top = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) top = fmaxf(top, fabsf(float(C[k])));
     float p[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};     // S = p0 + p1 cos + p2 sin + p3 cos 2phi + p4 sin 2phi
 #pragma unroll
     for (int m = 1; m < 3; ++m) {
@@ -323,33 +335,41 @@ __device__ __forceinline__ void scan_bounds(const R C[16], float& lo, float& hi)
         p[3] += 0.5f * (z[m][1] * z[m][1] - z[m][2] * z[m][2]);
         p[4] += z[m][1] * z[m][2];
     }
-    constexpr float h = 0.39269908f;
+    constexpr float h = 6.2831853f / kBoundDirs;
     const float t12 = __builtin_amdgcn_sqrtf(z[0][1] * z[0][1] + z[0][2] * z[0][2]);
     const float p12 = __builtin_amdgcn_sqrtf(p[1] * p[1] + p[2] * p[2]);
     const float p34 = __builtin_amdgcn_sqrtf(p[3] * p[3] + p[4] * p[4]);
     const float smin = p[0] - p12 - p34;
     const float eS = (p12 + 4.0f * p34) * (h * h / 8.0f), dS = (p12 + 2.0f * p34) * h;
-    constexpr float cs[16] = {1.0f, 0.92387953f, 0.70710678f, 0.38268343f, 0.0f, -0.38268343f, -0.70710678f, -0.92387953f,
-                              -1.0f, -0.92387953f, -0.70710678f, -0.38268343f, 0.0f, 0.38268343f, 0.70710678f, 0.92387953f};
+    constexpr float cs[kBoundDirs] = {1.0f, 0.91354546f, 0.66913061f, 0.30901699f, -0.10452846f, -0.50000000f,
+                                      -0.80901699f, -0.97814760f, -0.97814760f, -0.80901699f, -0.50000000f,
+                                      -0.10452846f, 0.30901699f, 0.66913061f, 0.91354546f};
+    constexpr float sn[kBoundDirs] = {0.0f, 0.40673664f, 0.74314483f, 0.95105652f, 0.99452190f, 0.86602540f,
+                                      0.58778525f, 0.20791169f, -0.20791169f, -0.58778525f, -0.86602540f,
+                                      -0.99452190f, -0.95105652f, -0.74314483f, -0.40673664f};
     lo = hi = -1e30f;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const float c = cs[k], s = cs[(k + 12) & 15], c2 = cs[(2 * k) & 15], s2 = cs[(2 * k + 12) & 15];
-        const float T = z[0][0] + z[0][1] * c + z[0][2] * s;
-        const float S = p[0] + p[1] * c + p[2] * s + p[3] * c2 + p[4] * s2;
-        lo = fmaxf(lo, T + __builtin_amdgcn_sqrtf(fmaxf(S, 0.0f)));
+    for (int k = 0; k < kBoundDirs; ++k) {
+        const float T = z[0][0] + z[0][1] * cs[k] + z[0][2] * sn[k];
+        const float B = z[1][0] + z[1][1] * cs[k] + z[1][2] * sn[k];
+        const float D = z[2][0] + z[2][1] * cs[k] + z[2][2] * sn[k];
+        const float S = B * B + D * D;
+        lo = fmaxf(lo, T + __builtin_amdgcn_sqrtf(S));
         hi = fmaxf(hi, T + __builtin_amdgcn_sqrtf(S + eS));
     }
-    hi += t12 * (h * h / 8.0f) + dS * dS * __builtin_amdgcn_rcpf(32.0f * smin * __builtin_amdgcn_sqrtf(smin));
-    if (!(smin > 1e-6f * p[0])) hi = __builtin_inff();
+    const float e = 4e-5f * top;
+    lo -= e;
+    // 1.01: the rounding of smin, at most 0.6 % where it is accepted
+    hi += t12 * (h * h / 8.0f) + 1.01f * dS * dS * __builtin_amdgcn_rcpf(32.0f * smin * __builtin_amdgcn_sqrtf(smin)) + e;
+    if (!(smin > 1e-4f * p[0])) hi = __builtin_inff();
 }
 
 // One partial row of LBM_DIAG_COUNT values per workgroup.  The direction scan of the acoustic
 // tensor (180 directions, some 10 000 instructions per node) was the whole cost: 4.06 ms of
 // 4096^2 in FP32.  Only nodes that can hold the workgroup's largest value take it now: those
-// whose bound (scan_bounds) reaches the largest sample seen so far, less 1e-4 of it, ten times
-// what the FP32 scan's rounding (the drift of its rotated direction) can move.  A wavefront
-// with few such nodes takes them one by one, its lanes sharing the directions.
+// whose upper bound reaches the largest lower bound seen so far (scan_bounds), so that the result
+// is that of the full scan, whatever the order in which that floor is raised.  A wavefront with
+// few such nodes takes them one by one, its lanes sharing the directions.
 template <int ST, int LAW, bool FIELDS>
 __global__ void __launch_bounds__(kBlock) diag_kernel(RecoverArgs a) {
     using Tr = Storage<ST>;
@@ -359,7 +379,7 @@ __global__ void __launch_bounds__(kBlock) diag_kernel(RecoverArgs a) {
     const Common& cm = a.cm;
     const int64_t n = int64_t(cm.nx) * cm.ny;
     __shared__ R dirs[2][kScanDirs];
-    __shared__ int floor_bits;                      // the largest sample, as the bits of a float >= 0
+    __shared__ int floor_bits;                      // the largest lower bound, as the bits of a float >= 0
     __shared__ double red[LBM_DIAG_COUNT][kBlock];
     if (threadIdx.x == 0) {
         floor_bits = 0;
@@ -412,7 +432,7 @@ __global__ void __launch_bounds__(kBlock) diag_kernel(RecoverArgs a) {
                 atomicMax(&floor_bits, __float_as_int(lo));
         }
         if (base == int64_t(blockIdx.x) * blockDim.x) __syncthreads();
-        const float thr = __int_as_float(*(volatile int*)&floor_bits) * (1.0f - 1e-4f);
+        const float thr = __int_as_float(*(volatile int*)&floor_bits);
         const bool odd = valid && !isfinite(hi);
         const uint64_t want = __ballot(valid && !(hi < thr));
         if (__ballot(odd) != 0 || __popcll(want) > 40) {
