@@ -302,13 +302,19 @@ __device__ __forceinline__ R acoustic_max(const R C[16], R n0, R n1) {
 // root of a linear S its own chord by (dS)^2 / (32 Smin^(3/2)).  Both bounds keep 4e-5 of the
 // largest |C_iAkB| apart from the samples: the FP32 scan's rotated directions drift by 5e-6 in
 // |n|^2 and 6e-7 in angle, and |Q| <= |C| (Frobenius, at most 4 times that entry); with the
-// rounding of either side that makes 8e-6 |C|.  hi is not finite where S may vanish or the state is not
+// rounding of either side that makes 8e-6 |C|.  All is formed for C divided by that entry: the
+// fourth powers of the moduli would leave FP32's range (of moduli of 1e-12 the bound was 0.3 %
+// below the scan).  hi is not finite where S may vanish or the state is not
 // finite: no bound.
 constexpr int kBoundDirs = 15;                       // every twelfth direction of the scan (18: 3 % slower)
 static_assert(kScanDirs % kBoundDirs == 0, "the samples are directions of the scan");
 
 template <typename R>
 __device__ __forceinline__ void scan_bounds(const R C[16], float& lo, float& hi) {
+    float top = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) top = fmaxf(top, fabsf(float(C[k])));
+    const float scale = __builtin_amdgcn_rcpf(top);
     float z[3][3];                                  // T, (Q00 - Q11)/2, (Q01 + Q10)/2
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
@@ -320,12 +326,9 @@ __device__ __forceinline__ void scan_bounds(const R C[16], float& lo, float& hi)
         };
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-            z[m][j] = m == 0 ? 0.5f * (coef(0, 0, j) + coef(1, 1, j))
-                    : m == 1 ? 0.5f * (coef(0, 0, j) - coef(1, 1, j)) : 0.5f * (coef(0, 1, j) + coef(1, 0, j));
+            z[m][j] = scale * (m == 0 ? 0.5f * (coef(0, 0, j) + coef(1, 1, j))
+                             : m == 1 ? 0.5f * (coef(0, 0, j) - coef(1, 1, j)) : 0.5f * (coef(0, 1, j) + coef(1, 0, j)));
     }
-    float top = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) top = fmaxf(top, fabsf(float(C[k])));
     float p[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};     // S = p0 + p1 cos + p2 sin + p3 cos 2phi + p4 sin 2phi
 #pragma unroll
     for (int m = 1; m < 3; ++m) {
@@ -357,11 +360,13 @@ __device__ __forceinline__ void scan_bounds(const R C[16], float& lo, float& hi)
         lo = fmaxf(lo, T + __builtin_amdgcn_sqrtf(S));
         hi = fmaxf(hi, T + __builtin_amdgcn_sqrtf(S + eS));
     }
-    const float e = 4e-5f * top;
-    lo -= e;
+    lo = top * (lo - 4e-5f);
     // 1.01: the rounding of smin, at most 0.6 % where it is accepted
-    hi += t12 * (h * h / 8.0f) + 1.01f * dS * dS * __builtin_amdgcn_rcpf(32.0f * smin * __builtin_amdgcn_sqrtf(smin)) + e;
-    if (!(smin > 1e-4f * p[0])) hi = __builtin_inff();
+    hi += t12 * (h * h / 8.0f) + 1.01f * dS * dS * __builtin_amdgcn_rcpf(32.0f * smin * __builtin_amdgcn_sqrtf(smin)) + 4e-5f;
+    hi *= top;
+    const bool in_range = top > 1e-30f && top < 1e30f;
+    if (!in_range || !(smin > 1e-4f * p[0])) hi = __builtin_inff();
+    if (!in_range) lo = 0.0f;
 }
 
 // One partial row of LBM_DIAG_COUNT values per workgroup.  The direction scan of the acoustic

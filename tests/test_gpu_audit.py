@@ -74,6 +74,20 @@ def test_a_peak_between_directions_does_not_hide_a_larger_scan():
     assert abs(got - want) <= TOL["f64"] * cond * want
 
 
+@pytest.mark.parametrize("scale", [1e-24, 1e-12, 1.0, 1e12, 1e24])
+def test_moduli_of_any_size(scale):
+    """The bounds are formed in FP32: their powers of the moduli must not leave its range."""
+    mu, lam = scale, 2.0 * scale
+    F = np.empty((2, 2, 3, 5))
+    B = np.array([[0.2093, -1.2362], [0.73, 0.5282]])
+    target = _scan("lognh", B[:, :, None], mu, lam)[0][0]
+    F[:] = _dilation("lognh", target * (1 - 1e-3), mu, lam, 1.4, 0.4) * np.eye(2)[:, :, None, None]
+    F[:, :, 2, 1] = B
+    got, want, cond = _audit("lognh", F, "f64", mu, lam, 8.0 * scale ** 0.5)
+    assert abs(want * want * 64.0 * scale / target - 1) < 1e-12
+    assert abs(got - want) <= TOL["f64"] * cond * want
+
+
 @pytest.mark.parametrize("storage", ["f32", "f64"])
 @pytest.mark.parametrize("amp", [0.02, 0.3, 1.0])
 @pytest.mark.parametrize("law", om.ALL_LAWS)
