@@ -24,7 +24,7 @@ from typing import Callable, Optional, Sequence
 import torch
 
 from . import _lib as L
-from .solver import EdgeData, Solver, _ptr, _stream, host_matrix, pack_edges
+from .solver import EdgeData, Solver, _ptr, _stream, call_edges, host_matrix
 
 
 @dataclass
@@ -40,7 +40,9 @@ class RolloutConfig:
     storage: str = "f32"
     bc: Sequence[str] = ("periodic",) * 4
     ramp: Callable[[int], float] = lambda n: 1.0      # r(n)
-    edges: Optional[Callable[[int], Sequence]] = None  # n -> data at t^{n+1/2} (4 pairs)
+    edges: Optional[Callable[[int], Sequence]] = None  # n -> data at t^{n+1/2} (4 pairs or (2, L)
+                                                       # tensors); called again by the replays, and
+                                                       # each call may refill what it returns
     u0: Optional[torch.Tensor] = None
     checkpoint_every: int = 100
     levels: Sequence[int] = field(default_factory=list)   # nested segment lengths, outermost first
@@ -373,15 +375,15 @@ class _Adjoint:
 
     def steps(self, sv, cfg, m, records):
         """lbm_adjoint_advance: levels m, m - 1, ..., m - len(records) + 1 by the fastest
-        launches; records[t] holds U^{m-t}."""
-        k = len(records)
-        r = (ctypes.c_double * k)(*[float(cfg.ramp(m - t)) for t in range(k)])
-        recs = (ctypes.c_void_p * k)(*[rec.data_ptr() for rec in records])
-        ed, held = None, []
-        if not sv.periodic:
-            ed = pack_edges([None if cfg.edges is None else cfg.edges(m - t) for t in range(k)], held)
-        L.check(sv.lib.lbm_adjoint_advance(ctypes.byref(sv.p), ctypes.byref(sv.s), ctypes.byref(self.a), int(m), int(k),
-                                           r, ed, recs, _stream()), "lbm_adjoint_advance")
+        launches, in calls of _blocks; records[t] holds U^{m-t}."""
+        for t0, t1 in _blocks(0, len(records)):
+            k, top = t1 - t0, m - t0
+            r = (ctypes.c_double * k)(*[float(cfg.ramp(top - t)) for t in range(k)])
+            recs = (ctypes.c_void_p * k)(*[rec.data_ptr() for rec in records[t0:t1]])
+            held = []
+            ed = _wall_data(sv, cfg, range(top, top - k, -1), held)
+            L.check(sv.lib.lbm_adjoint_advance(ctypes.byref(sv.p), ctypes.byref(sv.s), ctypes.byref(self.a), int(top),
+                                               int(k), r, ed, recs, _stream()), "lbm_adjoint_advance")
 
     def init(self, sv, cfg, v0, u0):
         L.check(sv.lib.lbm_adjoint_init(ctypes.byref(sv.p), ctypes.byref(sv.s), ctypes.byref(self.a), _ptr(v0),
@@ -426,11 +428,34 @@ def _auto(cfg):
     return cfg.pairs is None and cfg.multi is not False
 
 
+# steps per call of the library where it picks the launches: whole groups of 2, 3, 4, 6 and 8
+# levels, and a bound on the wall data that are held and on the host's delay before a launch
+_CALL_STEPS = 96
+
+
+def _blocks(n0, n1):
+    """[n0, n1) in pieces of _CALL_STEPS, the last one of less than twice as many."""
+    while n1 - n0 >= 2 * _CALL_STEPS:
+        yield n0, n0 + _CALL_STEPS
+        n0 += _CALL_STEPS
+    if n1 > n0:
+        yield n0, n1
+
+
+def _wall_data(sv, cfg, steps, held):
+    """The packed wall data of the given steps, None on a periodic grid."""
+    if sv.periodic:
+        return None
+    return call_edges(cfg.edges or (lambda n: None), steps, held)
+
+
 def _auto_steps(sv, cfg, n0, n1, records=None, ustar=True, record_planes=6):
-    """Steps n0 .. n1 - 1 by lbm_advance; records: one entry (or None) per step."""
-    edges = None if sv.periodic else [None if cfg.edges is None else cfg.edges(n) for n in range(n0, n1)]
-    sv.steps(n0, [float(cfg.ramp(n)) for n in range(n0, n1 + 1)], edges=edges, records=records, ustar=ustar,
-             record_planes=record_planes)
+    """Steps n0 .. n1 - 1 by lbm_advance, in calls of _blocks; records: one entry (or None) per
+    step."""
+    for a, b in _blocks(n0, n1):
+        held = []
+        sv._steps(a, [float(cfg.ramp(n)) for n in range(a, b + 1)], _wall_data(sv, cfg, range(a, b), held),
+                  None if records is None else records[a - n0:b - n0], ustar, record_planes)
 
 
 def _pairs(sv, cfg):

@@ -37,19 +37,26 @@ def fill_edges(c, values, keep):
             pair[1] = float(v[1])
 
 
-def pack_edges(edges, keep):
+def pack_edges(edges, keep, count=None, refilled=None):
     """The boundary data of consecutive half steps (four entries each, as fill_edges takes them,
     EdgeData or None) as a C array of lbm_edge_data: values are gathered in one Python list and
     converted at once (1 us per half step; element by element through ctypes it took 4, more than
-    a level of a small walled grid takes on the device)."""
-    n = len(edges)
+    a level of a small walled grid takes on the device).
+
+    edges is a sequence, or with `count` an iterator over as many calls of a user's function,
+    whose results may be one list or one tensor that each call fills anew: host values are read
+    before the next call.  Tensors are read by the launches, later: with refilled=False memory
+    that an earlier half step holds already gives None (the earlier data may be gone), and with
+    refilled=True every tensor is copied before the next call."""
+    n = len(edges) if count is None else count
     out = (L.lbm_edge_data * n)()
-    flat, special = [], []
+    flat, special, seen = [], [], {}
     add = flat.append
     for i, ed in enumerate(edges):
         if ed is None or isinstance(ed, EdgeData):
             if ed is not None:
-                special.append((i, ed))
+                special.append((i, L.lbm_edge_data.from_buffer_copy(ed.c)))
+                keep.append(ed)
             flat.extend((0.0,) * 8)
             continue
         for e in range(4):
@@ -60,7 +67,12 @@ def pack_edges(edges, keep):
             elif isinstance(v, torch.Tensor):
                 add(0.0)
                 add(0.0)
-                t = v.to(torch.float64).contiguous()
+                if refilled:
+                    t = v.to(torch.float64, copy=True, memory_format=torch.contiguous_format)
+                else:
+                    t = v.to(torch.float64).contiguous()
+                    if refilled is False and t.data_ptr() == v.data_ptr() and seen.setdefault(t.data_ptr(), i) != i:
+                        return None
                 keep.append(t)
                 out[i].field[e] = t.data_ptr()
             else:
@@ -68,8 +80,23 @@ def pack_edges(edges, keep):
                 add(float(v[1]))
     words = np.frombuffer(out, dtype=np.float64).reshape(n, ctypes.sizeof(L.lbm_edge_data) // 8)
     words[:, :8] = np.array(flat, dtype=np.float64).reshape(n, 8)
-    for i, ed in special:
-        out[i] = ed.c
+    for i, c in special:
+        out[i] = c
+    return out
+
+
+def call_edges(edges, steps, keep):
+    """The boundary data edges(n) of the half steps n in `steps` as pack_edges packs them, right
+    also where each call refills and returns the same tensor: then the data of these steps are
+    asked for once more and copied as they come (edges must be a function of n, which the replays
+    of a backward pass need anyway)."""
+    steps = list(steps)
+    held = []
+    out = pack_edges(map(edges, steps), held, len(steps), refilled=False)
+    if out is None:
+        held = []
+        out = pack_edges(map(edges, steps), held, len(steps), refilled=True)
+    keep.extend(held)
     return out
 
 
@@ -404,9 +431,13 @@ class Solver:
             raise ValueError("records needs one entry per step")
         if count < 1:
             return
-        ra = (ctypes.c_double * (count + 1))(*r)
         held = []
-        ea = None if edges is None else pack_edges(edges, held)
+        self._steps(n, r, None if edges is None else pack_edges(edges, held), records, ustar, record_planes)
+
+    def _steps(self, n, r, ea=None, records=None, ustar=True, record_planes=6):
+        """steps with packed edges (pack_edges)."""
+        count = len(r) - 1
+        ra = (ctypes.c_double * (count + 1))(*r)
         rec = None
         if records is not None:
             rec = (ctypes.c_void_p * count)(*[None if t is None else t.data_ptr() for t in records])
@@ -491,7 +522,9 @@ class Solver:
 
     def advance(self, n0, count, ramp=None, edges=None, block=64, fused=None, graph=None):
         """Steps n0 .. n0 + count - 1 with ramp factors ``ramp(n)`` (default 1) and wall data
-        ``edges(n)`` (default zero).  With ``graph`` True, whole blocks of ``block`` steps
+        ``edges(n)`` (default zero).  ``edges`` is called once per step, for a block of steps
+        before their launches: device tensors that it returns must keep their values until
+        advance returns (host values may be refilled by each call).  With ``graph`` True, whole blocks of ``block`` steps
         whose arguments equal those of the first captured block replay one captured graph
         and the rest run eagerly; this removes the per-step host cost where it dominates.
         On grids of more than GRAPH_MAX_NODES nodes eager launches already follow each other
@@ -509,8 +542,9 @@ class Solver:
             end, n = n0 + count, n0
             while n < end:
                 m = min(end, n + max(16, block))
-                walls = None if self.periodic else [edges(k) for k in range(n, m)]
-                self.steps(n, [float(ramp(k)) for k in range(n, m + 1)], edges=walls)
+                held = []
+                walls = None if self.periodic else pack_edges(map(edges, range(n, m)), held, m - n)
+                self._steps(n, [float(ramp(k)) for k in range(n, m + 1)], walls)
                 n = m
             return
         fused = self.pairs_pay if fused is None else (bool(fused) and self.pairs_ok)
