@@ -535,6 +535,74 @@ PatchPlan patch_choice(const lbm_params* p, const PatchCost& c, int words, bool 
     return best;
 }
 
+// Periodic grids of about 280^2 nodes and more, where one launch takes two or more patches per
+// compute unit: the model above misses how the patches of a unit share it, and there the plan was
+// read off sweeps instead.  The first entry that holds the storage, the law and the grid's side
+// sqrt(nx ny) decides; levels = 0: pairs of levels.  Measured on all plans and the pairs over grids
+// of 1:1, 4:1 and 1:4, uniform and per-node parameters, log-NH, svk, MR, Yeoh and Gent (times over
+// the best of all, averaged over the grids of a size): the model's plans reach 1.48 and, where the
+// pairs are better, were up to 1.54 times as slow as these.
+struct PlanRange {
+    int storage, laws;               // laws: bits of the materials
+    int lo, hi;                      // sides [lo, hi)
+    PatchPlan plan;
+};
+constexpr int kLameLaws = 1 << LBM_LOGNH | 1 << LBM_NH | 1 << LBM_SVK;
+constexpr int kInvariantLaws = 1 << LBM_MR | 1 << LBM_YEOH | 1 << LBM_GENT;
+constexpr int kAllLaws = kLameLaws | kInvariantLaws;
+
+const PlanRange kForwardRanges[] = {
+    // this 1.00 to 1.03 (at 352^2 1.09), model 1.00 to 1.10, pairs 1.00 to 1.47
+    {LBM_F32_SHIFTED, kLameLaws, 354, 440, {4, 32, 12}},
+    // pairs 1.00 to 1.07, model 1.04 to 1.31, {4, 32, 12} 1.00 to 1.18; from 400^2 on pairs 1.01 to 1.35
+    {LBM_F32_SHIFTED, kInvariantLaws, 354, 388, {0, 0, 0}},
+    {LBM_F32_SHIFTED, kInvariantLaws, 395, 430, {4, 32, 12}},
+    // 1.00 to 1.02, model 1.02 to 1.22, pairs 1.41 to 1.51 (610^2 to 690^2 1.00 / 1.02 to 1.09; 700^2
+    // the other way, 1.05 / 1.00)
+    {LBM_F32_SHIFTED, kAllLaws, 720, 1 << 15, {3, 32, 8}},
+    // 1.00 to 1.02, model 1.01 to 1.13, pairs 1.02 to 1.15 (at 350^2 1.10 / 1.00); Yeoh: pairs 1.00 to
+    // 1.03, model 1.08 to 1.27
+    {LBM_F16_SHIFTED, kAllLaws & ~(1 << LBM_YEOH), 354, 435, {4, 32, 12}},
+    {LBM_F16_SHIFTED, 1 << LBM_YEOH, 354, 435, {0, 0, 0}},
+    // pairs 1.00 to 1.03, model 1.00 to 1.31, {3, 32, 8} 1.05 to 1.16: up to here the two buffers of
+    // the pairs fit the L2s of the eight dies (32 MB); at 430^2 pairs 1.10, model 1.00; at 580^2
+    // 1.07 / 1.01
+    {LBM_F16_SHIFTED, kAllLaws, 435, 577, {0, 0, 0}},
+    // 1.02 to 1.07, model 1.00 to 1.14, pairs 1.16 to 1.24
+    {LBM_F16_SHIFTED, kAllLaws, 720, 1 << 15, {3, 32, 8}},
+    // per-node Yeoh: pairs 1.00, {3, 16, 8} 1.07 to 1.09, model 1.11 to 1.16
+    {LBM_F64_PLAIN, 1 << LBM_YEOH, 365, 390, {0, 0, 0}},
+    // 1.00 to 1.10, model 1.01 to 1.24, pairs 1.00 to 1.55 (272^2: 1.03 to 1.09 / 1.00 to 1.05)
+    {LBM_F64_PLAIN, kAllLaws, 285, 1 << 15, {3, 16, 8}},
+};
+const PlanRange kAdjointRanges[] = {
+    // pairs 1.00 to 1.04 (383^2 log-NH 1.08), model 1.05 to 1.28, {3, 16, 8} 1.04 to 1.11
+    {LBM_F32_SHIFTED, kLameLaws, 310, 390, {0, 0, 0}},
+    // pairs 1.00, model 1.00 to 1.12 (Gent 1.01 to 1.09 / 0.98 to 1.06)
+    {LBM_F32_SHIFTED, 1 << LBM_MR | 1 << LBM_YEOH, 335, 388, {0, 0, 0}},
+    // 1.00 to 1.03, model 0.99 to 1.17, pairs 1.02 to 1.55
+    {LBM_F64_PLAIN, kLameLaws, 285, 1 << 15, {3, 16, 8}},
+    // Gent: pairs 1.00 to 1.06, model 1.07 to 1.13
+    {LBM_F64_PLAIN, 1 << LBM_GENT, 312, 388, {0, 0, 0}},
+    // Yeoh: pairs 1.00 to 1.09, model 1.08 to 1.20 (at 200^2 1.04 / 1.01, at 279^2 1.23 / 1.00, at
+    // 392^2 1.09 / 1.00)
+    {LBM_F64_PLAIN, 1 << LBM_YEOH, 210, 268, {0, 0, 0}},
+    {LBM_F64_PLAIN, 1 << LBM_YEOH, 302, 388, {0, 0, 0}},
+};
+
+// The entry for a periodic grid (nullptr: the model decides), on grids no narrower than those of
+// the sweeps.
+template <int N>
+const PatchPlan* ranged_plan(const lbm_params* p, int storage, const PlanRange (&ranges)[N]) {
+    if (p->nx < 2 * kTile || p->ny < kTile) return nullptr;
+    const int64_t nodes = int64_t(p->nx) * p->ny;
+    for (const PlanRange& r : ranges)
+        if (r.storage == storage && (r.laws >> p->material & 1) && nodes >= int64_t(r.lo) * r.lo &&
+            nodes < int64_t(r.hi) * r.hi)
+            return &r.plan;
+    return nullptr;
+}
+
 // The plan of patch_kernel.  Where it stops (side) the other kernels are faster.  Measured us
 // per level, patches against the pairs, single steps and multi-level launches they replace
 // (log-NH, uniform parameters):
@@ -550,7 +618,9 @@ PatchPlan patch_choice(const lbm_params* p, const PatchCost& c, int words, bool 
 //   FP64 traction  64^2 8.9 / 15.1, 256^2 9.1 / 16.3, 640^2 19.7 / 36.9, 850^2 39.8 / 38.1
 //   FP64 velocity  64^2 3.2 / 5.6, 256^2 4.8 / 7.2, 640^2 14.3 / 27.2, 850^2 33.6 / 29.6
 // (the traction solves of a wall node, some 700 dependent instructions per level, bound the
-// small walled grids).
+// small walled grids).  FP16 has no fit of its own: it takes kShifted's constants and, with traction
+// edges, kTraction's (those plans are 1.06 to 1.22 times the best on 256^2 to 1090^2, the pairs 1.38
+// to 2.08).
 PatchPlan patch_plan(const lbm_params* p) {
     static const PatchCost kShifted{12.7, 0.84, 0.457, 3.43, 1.0, 0.92, 1024, patch_threads(false, false), 24};
     static const PatchCost kVelocity{2.80, 0.306, 0.032, 0.600, 1.0, 0.92, 1100, patch_threads(false, false), 24};
@@ -562,16 +632,15 @@ PatchPlan patch_plan(const lbm_params* p) {
     const bool walls = any_wall(p), traction = has_traction(p);
     const bool plain = p->storage == LBM_F64_PLAIN, half = p->storage == LBM_F16_SHIFTED;
     const int64_t nodes = int64_t(p->nx) * p->ny;
-    // FP16 pairs move half the bytes: they win where their grids fit the caches (638 x 339: 4.3
-    // us per level, patches 5.4; 404^2 and 584^2 are 3 and 17 % slower in pairs)
-    if (half && !walls && nodes > 430 * 430 && nodes < 530 * 530) return PatchPlan{0, 0, 0};
     const PatchCost& c = plain ? (traction ? kPlainTraction : kPlain)
                                : traction ? kTraction
                                           : half ? (walls ? kHalfVelocity : kHalf) : (walls ? kVelocity : kShifted);
-    // large grids: many rounds of small workgroups, three to a compute unit (1000 x 777: 11.8 us
-    // per level, 13.9 with the least-cost plan)
-    if (!plain && !walls && nodes > 720 * 720 && nodes <= int64_t(c.side) * c.side && p->nx >= 32)
-        return PatchPlan{3, 32, std::min(8, p->ny)};
+    if (nodes > int64_t(c.side) * c.side) return PatchPlan{0, 0, 0};
+    if (!walls)
+        if (const PatchPlan* r = ranged_plan(p, p->storage, kForwardRanges)) return *r;
+    // FP16 between velocity walls, all laws: this 1.00 to 1.01, model 1.10 to 1.17, pairs 1.14 to 1.24
+    if (half && walls && !traction && nodes >= 365 * 365 && nodes < 400 * 400)
+        return PatchPlan{3, std::min(16, p->nx), std::min(8, p->ny)};
     return patch_choice(p, c, traction ? 27 : 25, false);
 }
 
@@ -740,10 +809,25 @@ PatchPlan patch_adj_plan(const lbm_params* p) {
     static const PatchCost kInvShiftedWalls{3.09, 37.5, 4.19, 6.26, 0.55, 1.0, 1030, kPatchAdjThreads, 24};
     static const PatchCost kInvPlain{10.8, 20.7, 2.81, 1.91, 0.90, 1.0, 420, kPatchAdjThreads, 12};
     static const PatchCost kInvPlainWalls{3.77, 13.0, 1.50, 2.38, 1.0, 1.0, 700, kPatchAdjThreads, 12};
-    const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN;
+    const bool walls = any_wall(p), plain = p->storage == LBM_F64_PLAIN, traction = has_traction(p);
     const PatchCost& c = invariant_material(p)
                              ? (plain ? (walls ? kInvPlainWalls : kInvPlain) : (walls ? kInvShiftedWalls : kInvShifted))
                              : (plain ? (walls ? kPlainWalls : kPlain) : (walls ? kShiftedWalls : kShifted));
+    // Smaller limits (patches / pairs, over the better one).  The FP64 kernels of MR and Yeoh keep up
+    // to 99 of their registers in scratch memory: periodic MR 128^2 1.00 / 1.03, 180^2 1.09 / 1.00,
+    // 340^2 1.44 / 1.00.  FP64 between velocity walls (a channel and four walls): MR 580^2 1.00 /
+    // 1.02, 640^2 1.05 / 1.00; Yeoh 580^2 1.00 / 1.08, 700^2 1.12 / 1.00; Gent 640^2 1.00 / 1.01,
+    // 700^2 1.07 / 1.00.  FP32 between velocity walls: MR and Yeoh 750^2 1.00 / 1.04, 820^2 1.05 /
+    // 1.00, 1000^2 1.17 / 1.00; the Lame-type laws 1099^2 1.00 / 1.10, 1200^2 1.08 / 1.00.
+    const bool mr = p->material == LBM_MR, yeoh = p->material == LBM_YEOH;
+    int side = c.side;
+    if (plain && !walls && mr) side = 150;
+    if (plain && walls && !traction && invariant_material(p)) side = mr ? 590 : yeoh ? 630 : 690;
+    if (!plain && walls && !traction) side = mr || yeoh ? 800 : invariant_material(p) ? side : 1130;
+    const int64_t nodes = int64_t(p->nx) * p->ny;
+    if (nodes > int64_t(side) * side) return PatchPlan{0, 0, 0};
+    if (!walls)
+        if (const PatchPlan* r = ranged_plan(p, plain ? LBM_F64_PLAIN : LBM_F32_SHIFTED, kAdjointRanges)) return *r;
     return patch_choice(p, c, 25, walls);
 }
 

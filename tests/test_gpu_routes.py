@@ -64,3 +64,24 @@ def test_adjoint_above_its_patches(walls):
 def test_adjoint_march():
     adjoint.compare(2051, 2049, "f32", "lognh", "periodic", True, 18, 18, 10)
     adjoint.compare(2051, 2049, "f32", "gent", "periodic", True, 18, 17, 8)
+
+
+@pytest.mark.parametrize("storage,nx,ny", [("f32", 360, 361), ("f32", 396, 410), ("f16", 399, 370), ("f64", 375, 380),
+                                           ("f64", 291, 300), ("f64", 128, 900)])
+def test_ranged_plans(storage, nx, ny):
+    """Periodic grids whose plan, or pairs instead, was read off sweeps."""
+    compare(nx, ny, storage, "lognh", "periodic", True, 9, n0=11)
+    compare(nx, ny, storage, "yeoh", "periodic", True, 8, records=4)
+
+
+def test_half_precision_between_velocity_walls():
+    compare(381, 390, "f16", "lognh", "all_velocity", True, 7, n0=13)
+
+
+@pytest.mark.parametrize("storage,law,walls,nx,ny",
+                         [("f32", "svk", "periodic", 340, 352), ("f32", "yeoh", "periodic", 361, 350),
+                          ("f64", "svk", "periodic", 321, 300), ("f64", "gent", "periodic", 340, 333),
+                          ("f64", "yeoh", "periodic", 230, 240), ("f64", "mr", "periodic", 190, 200),
+                          ("f32", "mr", "x_channel", 851, 830), ("f64", "yeoh", "all_velocity", 661, 650)])
+def test_ranged_adjoint_plans(storage, law, walls, nx, ny):
+    adjoint.compare(nx, ny, storage, law, walls, True, 19, 19, 10)
