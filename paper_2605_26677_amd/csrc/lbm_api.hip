@@ -644,56 +644,6 @@ PatchPlan patch_plan(const lbm_params* p) {
     return patch_choice(p, c, traction ? 27 : 25, false);
 }
 
-enum Route { kRouteStep, kRoutePair, kRouteMulti, kRouteRim, kRoutePatch };
-
-// Nodes from which a grid with walls takes the march of its inner rectangle, without records and
-// with (FP32 log-NH, two traction-free pairs of edges, us per level, march and patches around it
-// against patches alone and pairs: 1050^2 25 / 23 / 34, 1250^2 33 / 49 / 44; 2200^2 73 / - / 120;
-// 4096^2 with per-node mu and lam 0.23 ms / - / 0.43).
-constexpr int64_t kRimNodes = 1100 * 1100, kRimRecNodes = 1100 * 1100;
-
-// The launch that takes the next of `left` steps, and its levels (records: as lbm_advance's,
-// from the next step on, or NULL; patch: patch_plan).
-Route advance_route(const lbm_params* p, const lbm_state* s, const PatchPlan& patch, int64_t left,
-                    void* const* records, PatchPlan& pl) {
-    pl = PatchPlan{1, 0, 0};
-    if (s->body_prev) return kRouteStep;
-    if (patch.levels) {
-        pl = patch;
-        pl.levels = int(std::min<int64_t>(patch.levels, left));
-        return kRoutePatch;
-    }
-    const int64_t nodes = int64_t(p->nx) * p->ny;
-    const bool walls = any_wall(p);
-    if (left >= 2) {
-        // march_kernel: without records (4 levels, or what is left without leaving a single step
-        // over) and, in the shifted storages, with a record of every level; on a grid with walls
-        // its inner rectangle, and the patches the rest
-        const bool f64 = p->storage == LBM_F64_PLAIN;
-        int levels = int(std::min<int64_t>(kMarchMaxLevels, left)), recs = 0;
-        for (int t = 0; records && t < levels; ++t) recs += records[t] != nullptr;
-        bool go;
-        if (f64) {
-            const int side = invariant_material(p) ? (walls ? 1250 : 1100) : (walls ? 850 : 750);
-            go = recs == 0 && s->ustar && levels > 2 && nodes >= int64_t(side) * side;
-        } else if (recs == 0) {
-            go = s->ustar && nodes >= (walls ? kRimNodes : 1024 * 1024);
-        } else {
-            go = recs == kMarchMaxLevels && !s->ustar && nodes >= (walls ? kRimRecNodes : 2048 * 2048);
-        }
-        if (go && (!walls || (p->nx >= 4 * kTile && p->ny >= 4 * kTile))) {
-            pl.levels = recs == 0 && left - levels == 1 && levels > 2 ? levels - 1 : levels;
-            pl.pw = pl.ph = 16;
-            return walls ? kRouteRim : kRouteMulti;
-        }
-    }
-    if (left >= 2 && (!walls || nodes >= 416 * 416)) {
-        pl.levels = 2;
-        return kRoutePair;
-    }
-    return kRouteStep;
-}
-
 // The rectangle of a walled grid that the multi-level kernels take (march_kernel; the patches
 // take the rest): whole tiles and rows at least `levels` nodes away from every wall line.
 struct Inner {
@@ -712,6 +662,138 @@ Inner inner_rect(const lbm_params* p, int levels, int ph) {
         in.row1 = p->ny - ph;
     }
     return in;
+}
+
+// Side of the patches around the rectangle.
+constexpr int kRimPatch = 16;
+
+// us per level of four levels by march_kernel (with patches around its rectangle on a grid with
+// walls) and of two levels by the pairs, from what the launches do: the march wins where the
+// rectangle fills its spans, and loses on narrow grids and where the patches beside it cost more
+// than it saves.
+//   march: launch (with patches) + iteration * (iterations of a workgroup) + node * (nodes of the
+//          rectangle, repeated rows included) + rim * (nodes of the patches; between velocity walls,
+//          with traction) + link * (traction links)
+//   pairs: pair + tile * (nodes of whole tiles) + node2 * nodes + link2 * (links of velocity walls,
+//          of traction walls)
+// Nodes in millions, links in 10 000.  Fitted to 2 886 grids without records and 1 008 with a record
+// of every level (seven wall layouts, widths of 64 to 4500, log-NH and Gent, uniform and per-node
+// parameters).  On those and 2 886 more (svk, MR, Yeoh) the pick, which favours the march by 3 %, is
+// 0.1 to 1.1 % slower than the better one on average; the march everywhere was 0.1 to 8 % slower, up to
+// 1.98 times (FP64 MR, periodic, 64 columns; 257 columns between traction walls 1.79; FP16 Yeoh
+// 1.47).  FP32 with the Lame-type laws has no entry: the march was 1.00 to 1.82 times as fast.
+struct MarchCost {
+    int storage, laws, records;
+    double launch, iteration, node, rim[2], link;
+    double pair, tile, node2, link2[2];
+};
+const MarchCost kMarchCosts[] = {
+    {LBM_F64_PLAIN, kLameLaws, 0, 4.42, 0.94, 5.17, {52.56, 81.77}, 18.15, 6.49, 19.40, 20.72, {13.84, 28.44}},
+    {LBM_F64_PLAIN, kInvariantLaws, 0, 4.54, 1.36, 3.45, {59.03, 96.04}, 35.17, 9.81, 21.69, 19.02, {12.15, 25.25}},
+    {LBM_F16_SHIFTED, kLameLaws, 0, 2.41, 0.83, 3.46, {22.32, 25.04}, 5.56, 5.33, 15.88, 0.0, {5.62, 12.88}},
+    {LBM_F16_SHIFTED, kLameLaws, 1, 2.49, 0.90, 3.32, {28.84, 33.98}, 3.30, 5.56, 19.47, 0.0, {6.67, 14.84}},
+    {LBM_F16_SHIFTED, kInvariantLaws, 0, 2.45, 1.02, 4.20, {20.78, 28.06}, 8.70, 6.20, 16.63, 0.0, {5.27, 13.71}},
+    {LBM_F16_SHIFTED, kInvariantLaws, 1, 2.14, 1.13, 3.30, {27.37, 36.27}, 6.30, 6.17, 20.33, 0.0, {5.80, 15.44}},
+    {LBM_F32_SHIFTED, kInvariantLaws, 0, 1.97, 0.89, 5.23, {23.91, 28.44}, 8.85, 4.96, 13.38, 7.86, {7.19, 15.73}},
+    {LBM_F32_SHIFTED, kInvariantLaws, 1, 2.17, 1.02, 5.23, {26.79, 32.92}, 6.99, 5.45, 17.50, 7.79, {8.11, 16.79}},
+};
+
+// Whether the march is expected to be faster than the pairs (march_kernel's grids with walls, and
+// FP64 on periodic ones).
+bool march_pays(const lbm_params* p, bool records) {
+    const MarchCost* c = nullptr;
+    for (const MarchCost& m : kMarchCosts)
+        if (m.storage == p->storage && (m.laws >> p->material & 1) && m.records == int(records)) c = &m;
+    if (!c) return true;
+    const Inner in = inner_rect(p, kMarchMaxLevels, kRimPatch);
+    const int rows = in.row1 - in.row0;
+    int nspan, seg, nwg;
+    FastDiv d;
+    if (in.tile1 <= in.tile0 || rows < 1 ||
+        !march_geometry(in.tile1 - in.tile0, march_tiles(p->storage == LBM_F64_PLAIN), rows, kMarchMaxLevels, nspan,
+                        seg, nwg, d))
+        return false;
+    const int cus = compute_units(), halo = 2 * (kMarchMaxLevels - 1);
+    const double nodes = double(p->nx) * p->ny;
+    const double inner = double(rows) * (std::min(in.tile1 * kTile, p->nx) - in.tile0 * kTile);
+    double links[2] = {0.0, 0.0};                // of velocity and of traction walls
+    for (int e = 0; e < 4; ++e)
+        if (p->bc[e] != LBM_PERIODIC) links[p->bc[e] == LBM_TRACTION] += edge_len(p->nx, p->ny, e);
+    double march = c->iteration * ((nwg + cus - 1) / cus) * (seg + halo) + c->node * 1e-6 * inner * (seg + halo) / seg;
+    if (any_wall(p)) march += c->launch + c->rim[links[1] > 0.0] * 1e-6 * (nodes - inner) + c->link * 1e-4 * links[1];
+    const double tiles = double((p->nx + kTile - 1) / kTile) * kTile * p->ny;
+    const double pairs = c->pair + c->tile * 1e-6 * tiles + c->node2 * 1e-6 * nodes +
+                         1e-4 * (c->link2[0] * links[0] + c->link2[1] * links[1]);
+    return march < 1.03 * pairs;
+}
+
+enum Route { kRouteStep, kRoutePair, kRouteMulti, kRouteRim, kRoutePatch };
+
+// Nodes from which a grid with walls may take the march of its inner rectangle (FP32 log-NH, two
+// traction-free pairs of edges, us per level, march and patches around it against patches alone
+// and pairs: 1050^2 25 / 23 / 34, 1250^2 33 / 49 / 44; 2200^2 73 / - / 120; 4096^2 with per-node mu
+// and lam 0.23 ms / - / 0.43).
+constexpr int64_t kRimNodes = 1100 * 1100;
+
+// What a call of lbm_advance forms once: the patch plan (levels = 0: none), and whether march_kernel
+// takes the grid, without records and with a record of every level.
+struct AdvancePlan {
+    PatchPlan patch;
+    bool march, replay;
+};
+
+AdvancePlan advance_plan(const lbm_params* p) {
+    AdvancePlan a{patch_plan(p), false, false};
+    if (a.patch.levels) return a;
+    const bool walls = any_wall(p), f64 = p->storage == LBM_F64_PLAIN;
+    const int64_t nodes = int64_t(p->nx) * p->ny;
+    if (walls && (p->nx < 4 * kTile || p->ny < 4 * kTile)) return a;
+    if (f64) {
+        const int side = invariant_material(p) ? (walls ? 1250 : 1100) : (walls ? 850 : 750);
+        a.march = nodes >= int64_t(side) * side && march_pays(p, false);
+    } else if (walls) {
+        a.march = nodes >= kRimNodes && march_pays(p, false);
+        a.replay = nodes >= kRimNodes && march_pays(p, true);
+    } else {
+        a.march = nodes >= 1024 * 1024;
+        a.replay = nodes >= 2048 * 2048;
+    }
+    return a;
+}
+
+// The launch that takes the next of `left` steps, and its levels (records: as lbm_advance's,
+// from the next step on, or NULL).
+Route advance_route(const lbm_params* p, const lbm_state* s, const AdvancePlan& plan, int64_t left,
+                    void* const* records, PatchPlan& pl) {
+    pl = PatchPlan{1, 0, 0};
+    if (s->body_prev) return kRouteStep;
+    if (plan.patch.levels) {
+        pl = plan.patch;
+        pl.levels = int(std::min<int64_t>(plan.patch.levels, left));
+        return kRoutePatch;
+    }
+    const int64_t nodes = int64_t(p->nx) * p->ny;
+    const bool walls = any_wall(p);
+    if (left >= 2) {
+        // march_kernel: without records (4 levels, or what is left without leaving a single step
+        // over) and, in the shifted storages, with a record of every level; on a grid with walls
+        // its inner rectangle, and the patches the rest
+        const int levels = int(std::min<int64_t>(kMarchMaxLevels, left));
+        int recs = 0;
+        for (int t = 0; records && t < levels; ++t) recs += records[t] != nullptr;
+        const bool go = recs == 0 ? plan.march && s->ustar && (levels > 2 || p->storage != LBM_F64_PLAIN)
+                                  : plan.replay && recs == kMarchMaxLevels && !s->ustar;
+        if (go) {
+            pl.levels = recs == 0 && left - levels == 1 && levels > 2 ? levels - 1 : levels;
+            pl.pw = pl.ph = kRimPatch;
+            return walls ? kRouteRim : kRouteMulti;
+        }
+    }
+    if (left >= 2 && (!walls || nodes >= 416 * 416)) {
+        pl.levels = 2;
+        return kRoutePair;
+    }
+    return kRouteStep;
 }
 
 // The patches of the whole grid, those whose region reaches a wall first (their traction solves
@@ -869,7 +951,7 @@ extern "C" {
 int lbm_advance_levels(const lbm_params* p, const lbm_state* s, int64_t left, void* const* records) {
     if (lbm_check_params(p) != LBM_OK || !s || left < 1) return 0;
     PatchPlan pl;
-    advance_route(p, s, patch_plan(p), left, records, pl);
+    advance_route(p, s, advance_plan(p), left, records, pl);
     return pl.levels;
 }
 
@@ -881,13 +963,13 @@ lbm_status lbm_advance(const lbm_params* p, lbm_state* s, int64_t n, int64_t cou
     if (count < 0 || !r) return LBM_ERR_ARG;
     if (any_wall(p) && (!edges || !s->aux)) return LBM_ERR_ARG;
     if (records && record_planes != 6 && record_planes != 4) return LBM_ERR_ARG;
-    const PatchPlan patch = patch_plan(p);
+    const AdvancePlan plan = advance_plan(p);
     for (int64_t i = 0; i < count;) {
         const int64_t left = count - i;
         void* const* rec = records ? records + i : nullptr;
         const lbm_edge_data* ed = edges ? edges + i : nullptr;
         PatchPlan pl;
-        switch (advance_route(p, s, patch, left, rec, pl)) {
+        switch (advance_route(p, s, plan, left, rec, pl)) {
             case kRoutePatch: st = patch_launch(p, s, n + i, pl, r + i, ed, rec, record_planes, (hipStream_t)stream); break;
             case kRouteRim: {
                 const Inner in = inner_rect(p, pl.levels, pl.ph);
