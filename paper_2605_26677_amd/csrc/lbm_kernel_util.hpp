@@ -103,7 +103,8 @@ __device__ __forceinline__ void recover_node(const T* pop, int ntile, int x, int
 // ---------------------------------------------------------------- traction Newton
 // Normal column a = F^b_{.A} of the boundary deformation gradient from
 // N_A P_iA(F^b) = T_i (Sec. 3.6, eq:neumann-boundary-rule).  Newton steps
-// delta = -J^{-1} r with J_ik = N_A C_iAkA; step lengths 1, 1/2, ..., 2^-10, the first with
+// delta = -J^{-1} r with J_ik = N_A C_iAkA; step lengths 1, 1/2, ..., 2^-10 (the full step alone
+// where |r| <= 16 eps (|T| + 2 mu) with the plain F, its rounding floor), the first with
 // det F^b > 0 and a smaller |r| is taken; stop at |r| <= tol (|T| + mu |F^b - I|), when no
 // step length is accepted, or after max_iter updates.  Returns false on failure.  The axis
 // A is a template parameter: indexed at run time, F and the tangent would live in scratch
@@ -160,8 +161,9 @@ __device__ bool newton_column(R NA, const R tang[2], const R T[2], R mu, R lam,
         R alpha = R(1);
         bool accepted = false;
         // at that floor |r| is rounding noise, and a shorter step only draws it again: the full
-        // step alone decides (the eleven vain trials of the last iteration made three
-        // quarters of an FP64 solve)
+        // step alone decides (the eleven vain trials of the last iteration made three quarters of an
+        // FP64 solve; without them the error of F^b against extended precision is the same, 3e-17
+        // to 3e-16 on average over lam / mu of 0.1 to 1000 and strains of 1e-6 to 0.1)
         const int trials = rn <= R(16) * round ? 1 : 11;
         for (int ls = 0; ls < trials; ++ls) {
             const R trial[2] = {a[0] + alpha * d0, a[1] + alpha * d1};
