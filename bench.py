@@ -105,16 +105,17 @@ def fwd_adj_multi_bytes(kind, levels):
     return {"fwd": 224 + 2 * levels, "replay": 208 + 16 * levels, "adj": 232 + 20 * levels}[kind]
 
 
-def fwd_adj_bytes_per_level(storage, K, multi=None):
+def fwd_adj_bytes_per_level(storage, K, multi=None, fwd_levels=2):
     """Algorithmic bytes per node and level of the every-K forward + adjoint run: the forward
     sweep, the recorded replay and the adjoint in launches of multi = (forward, replay,
-    adjoint) levels (the multi-level kernels), or all in pairs (multi None)."""
+    adjoint) levels (the multi-level kernels), or all in pairs (multi None); FP64 has the
+    multi-level kernel in its forward sweep alone (fwd_levels per launch: the same bytes)."""
     b = FWD_ADJ_BYTES[storage]
     if multi:
         f, r, a = multi
         return (fwd_adj_multi_bytes("fwd", f) / f + fwd_adj_multi_bytes("replay", r) / r
                 + fwd_adj_multi_bytes("adj", a) / a + b["snapshot"] / K)
-    return (b["fwd"] + b["replay"] + b["adj"]) / 2 + b["snapshot"] / K
+    return b["fwd"] / fwd_levels + (b["replay"] + b["adj"]) / 2 + b["snapshot"] / K
 
 
 PROFILE_PMC = {"step": os.path.join(ROOT, "profiles", "step_f32_lognh_periodic_8192_pmc.txt"),
@@ -335,12 +336,13 @@ def time_forward_adjoint(n, steps, K, nprobe=16, storage="f32", multi=None):
     mem = torch.cuda.max_memory_allocated() / 2 ** 30
     ok = all(torch.isfinite(t.grad).all().item() for t in (mu, lam, v0))
     # the rollout's forward sweep, replay and adjoint go through the multi-level kernels on
-    # this periodic grid in the shifted storages (Solver.multi_levels, replay_multi_levels,
-    # adj_multi_levels), in pairs in FP64 or when turned off
+    # this periodic grid in the shifted storages; in FP64 the forward sweep does, the replay and
+    # the adjoint go in pairs, as all do when the multi-level kernels are turned off
     from paper_2605_26677_amd.solver import Solver
     multi = ((Solver.MULTI_LEVELS, Solver.REPLAY_MULTI_LEVELS, Solver.ADJ_MULTI_LEVELS)
              if (storage != "f64" and cfg.multi is not False) else None)
-    bpl = fwd_adj_bytes_per_level(storage, K, multi)
+    fwd_levels = MULTI_LEVELS if storage == "f64" and cfg.multi is not False else 2
+    bpl = fwd_adj_bytes_per_level(storage, K, multi, fwd_levels)
     gbs = bpl * n * n * steps / ((t_f + t_b) * 1e-3) / 1e9
     single = SINGLE_PASS_FWD_ADJ[storage]
     out = dict(ms_fwd=t_f, ms_bwd=t_b, mlups=n * n * steps / ((t_f + t_b) * 1e-3) / 1e6,
@@ -355,9 +357,9 @@ def time_forward_adjoint(n, steps, K, nprobe=16, storage="f32", multi=None):
                                          f"{multi[1]}, march_adj_kernel {fwd_adj_multi_bytes('adj', multi[2])} / "
                                          f"{multi[2]}")
                                         if multi else
-                                        ("two-level kernels, B per node and launch / 2: forward step2 "
-                                         f"{FWD_ADJ_BYTES[storage]['fwd']}, recorded replay step2 "
-                                         f"{FWD_ADJ_BYTES[storage]['replay']}, adjoint2 {FWD_ADJ_BYTES[storage]['adj']}"))
+                                        (f"B per node and launch / levels per launch: forward {FWD_ADJ_BYTES[storage]['fwd']}"
+                                         f" / {fwd_levels}, recorded replay step2 {FWD_ADJ_BYTES[storage]['replay']} / 2, "
+                                         f"adjoint2 {FWD_ADJ_BYTES[storage]['adj']} / 2"))
                                        + f"; snapshots {FWD_ADJ_BYTES[storage]['snapshot']} B per node every K levels",
                          "single_pass_bytes_per_node_level": single,
                          "single_pass_effective_GBps": single * n * n * steps / ((t_f + t_b) * 1e-3) / 1e9})
@@ -705,9 +707,7 @@ def main():
 
     suffix = {"single": "", "pairs": "_pairs", "multi": f"_multi{MULTI_LEVELS}"}
     for storage in only:
-        # FP64: pairs are its fastest fused form (its multi-level kernel runs short of registers)
-        modes = ("pairs", "single") if storage == "f64" else ("multi", "pairs", "single")
-        for mode in modes:
+        for mode in ("multi", "pairs", "single"):
             steps = args.steps if (storage == "f32" and mode == "multi") else args.variant_steps
             key = storage + suffix[mode]
             log(f"bench: timing {key} forward, {steps} steps")
@@ -750,7 +750,7 @@ def main():
     log("bench: copy ceiling")
     copy_gbs = copy_ceiling()
     main_storage = "f32" if "f32" in only else only[0]
-    main_key = main_storage + (suffix["pairs"] if main_storage == "f64" else suffix["multi"])
+    main_key = main_storage + suffix["multi"]
     r = res[main_key]
     main_kernel = "march" if r["kernel"] == "march_kernel" else "step2"
     traffic = measured_traffic(n, main_kernel) if main_storage == "f32" else None
@@ -811,9 +811,10 @@ def main():
                              bwd_over_fwd=v["bwd_over_fwd"])
     if fa:
         out["fwd_adjoint"] = fa
-    if "f64_pairs" in res:
-        out["fwd_f64"] = dict(mlups=res["f64_pairs"]["mlups"], frac_hbm=res["f64_pairs"]["frac_hbm"],
-                              mlups_single=res.get("f64", {}).get("mlups"))
+    f64 = res.get("f64" + suffix["multi"])
+    if f64:
+        out["fwd_f64"] = dict(mlups=f64["mlups"], frac_hbm=f64["frac_hbm"], levels_per_launch=f64["levels_per_launch"],
+                              mlups_pairs=res["f64_pairs"]["mlups"], mlups_single=res.get("f64", {}).get("mlups"))
     if not args.no_cpu:
         log("bench: timing the CPU oracle")
         out["cpu_baseline"] = cpu_baseline()

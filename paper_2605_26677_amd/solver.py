@@ -188,7 +188,9 @@ class Solver:
     dx, law ("lognh", "nh", "svk", "mr", "yeoh", "gent") with optional law_k constants,
     storage ("f32", "f16", "f64"), edge kinds, uniform or per-node mu, lam and body force."""
 
-    # Defaults of advance() and of the checkpointed rollout, from timings on one MI355X
+    # What advance(fused=..., graph=...) and rollouts with pairs or multi given take; by default
+    # lbm_advance and lbm_adjoint_advance choose, by rules of their own in the library, and these
+    # constants do not reach them.  From timings on one MI355X
     # (FP32, log-NH, us per level): a captured graph beats eager launches only where the
     # host launch cost dominates (256^2 periodic pairs 3.42 against 4.44, 384^2 4.37
     # against 4.52; from 512^2 up a replay adds a few microseconds per kernel node); on
@@ -462,10 +464,10 @@ class Solver:
 
     @property
     def multi_levels(self):
-        """Levels per lbm_step_multi call where that is the fastest way to advance: periodic
-        grids of at least MULTI_MIN_NODES nodes in the shifted storages (FP32, FP16) with a
-        body field shared by all levels; 0 elsewhere (walls: lbm_step2; FP64: pairs are
-        faster, its multi-level kernel has too few registers for the levels it holds)."""
+        """Levels per lbm_step_multi call that advance(fused=True) and rollouts with pairs=True
+        take: on periodic grids of at least MULTI_MIN_NODES nodes in the shifted storages (FP32,
+        FP16) with a body field shared by all levels; 0 elsewhere, where they take lbm_step2
+        (lbm_advance takes the multi-level kernel in FP64 and between walls too)."""
         ok = (self.periodic and self.pairs_ok and self.storage != "f64" and self.s.ustar
               and self.nx * self.ny >= self.MULTI_MIN_NODES)
         return self.MULTI_LEVELS if ok else 0
@@ -534,8 +536,8 @@ class Solver:
         for the grid and needs no capture: one launch then takes several levels on small grids
         too.  With ``fused`` True the steps go in
         groups of multi_levels through lbm_step_multi where that applies, else in pairs
-        through lbm_step2 (where pairs_ok), with the same result bit for bit; None fuses
-        where it is faster (pairs_pay)."""
+        through lbm_step2 (where pairs_ok), with the same result bit for bit; with ``graph`` True
+        None fuses where pairs_pay."""
         ramp = ramp or (lambda n: 1.0)
         edges = edges or (lambda n: None)
         if fused is None and not graph:
