@@ -557,7 +557,7 @@ const PlanRange kForwardRanges[] = {
     // pairs 1.00 to 1.07, model 1.04 to 1.31, {4, 32, 12} 1.00 to 1.18; from 400^2 on pairs 1.01 to 1.35
     {LBM_F32_SHIFTED, kInvariantLaws, 354, 388, {0, 0, 0}},
     {LBM_F32_SHIFTED, kInvariantLaws, 395, 430, {4, 32, 12}},
-    // 1.00 to 1.02, model 1.02 to 1.22, pairs 1.41 to 1.51 (610^2 to 690^2 1.00 / 1.02 to 1.09; 700^2
+    // 1.00 to 1.02, model 1.03 to 1.19, pairs 1.41 to 1.51 (610^2 to 690^2 1.00 / 1.02 to 1.09; 700^2
     // the other way, 1.05 / 1.00)
     {LBM_F32_SHIFTED, kAllLaws, 720, 1 << 15, {3, 32, 8}},
     // 1.00 to 1.02, model 1.01 to 1.13, pairs 1.02 to 1.15 (at 350^2 1.10 / 1.00); Yeoh: pairs 1.00 to
@@ -568,7 +568,8 @@ const PlanRange kForwardRanges[] = {
     // the pairs fit the L2s of the eight dies (32 MB); at 430^2 pairs 1.10, model 1.00; at 580^2
     // 1.07 / 1.01
     {LBM_F16_SHIFTED, kAllLaws, 435, 577, {0, 0, 0}},
-    // 1.02 to 1.07, model 1.00 to 1.14, pairs 1.16 to 1.24
+    // 1.02 to 1.07, model 1.00 to 1.14, pairs 1.16 to 1.24 (per-node Gent and Yeoh: pairs 3 to 8 %
+    // faster without records, 5 to 10 % slower with them)
     {LBM_F16_SHIFTED, kAllLaws, 720, 1 << 15, {3, 32, 8}},
     // per-node Yeoh: pairs 1.00, {3, 16, 8} 1.07 to 1.09, model 1.11 to 1.16
     {LBM_F64_PLAIN, 1 << LBM_YEOH, 365, 390, {0, 0, 0}},
