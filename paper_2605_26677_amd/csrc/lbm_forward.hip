@@ -374,9 +374,12 @@ __device__ __forceinline__ void scan_bounds(const R C[16], float& lo, float& hi)
 // 4096^2 in FP32.  Only nodes that can hold the workgroup's largest value take it now: those
 // whose upper bound reaches the largest lower bound seen so far (scan_bounds), so that the result
 // is that of the full scan, whatever the order in which that floor is raised.  A wavefront with
-// few such nodes takes them one by one, its lanes sharing the directions.
+// few such nodes takes them one by one, its lanes sharing the directions.  Four wavefronts per
+// SIMD in the shifted storages: at most 128 registers, which costs no spills.  The laws of the
+// invariants took up to 138, and with them three: FP32 at 739 x 396 with per-node moduli, us per
+// call, MR 37 -> 31, Yeoh 36 -> 32, Gent 37 -> 32; 1500 x 1100 78 -> 73, 76 -> 70, 78 -> 71.
 template <int ST, int LAW, bool FIELDS>
-__global__ void __launch_bounds__(kBlock) diag_kernel(RecoverArgs a) {
+__global__ void __launch_bounds__(kBlock, ST == LBM_F64_PLAIN ? 1 : 4) diag_kernel(RecoverArgs a) {
     using Tr = Storage<ST>;
     using R = typename Tr::real;
     using T = typename Tr::pop_t;
